@@ -127,6 +127,7 @@ struct WalkArgs {
     int32_t strategy;
     int32_t lds_cap;
     int32_t item_bytes;         // col (+ h) (+ label) per scanned or proposed edge
+    int32_t wave_lanes;         // lanes of each wave that take walkers (set by launch_walk from n and the grid)
     int32_t tick_steps;         // resumable walks: steps per walker per launch
     int32_t bound;              // 1: Node2Vec split eRJS bound (symmetric graphs only)
     const uint4 *mtab;          // edge index (8 uint4 per bucket) or null: search the sorted rows
@@ -202,7 +203,7 @@ hipError_t launch_profile(const WalkArgs &a, int kind, bool weighted, bool rjs_s
 hipError_t launch_profile_pick(const int64_t *row_ptr, int64_t stride, int n, int2 *out, hipStream_t s);
 // Persistent grid filling the device: resident blocks per CU (of the counter-free kernel
 // variant the launch takes: batched, eRVS-only (strategy FW_RVS_ONLY, single query) or the
-// general one) times the CUs, at most one block per 256 walkers.
+// general one) times the CUs, at most one wave per walker.
 int walk_grid(int kind, bool weighted, bool batch, int lds_cap, int64_t n, bool rvs_only = false);
 
 }  // namespace fw

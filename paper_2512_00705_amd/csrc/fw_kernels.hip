@@ -20,6 +20,8 @@
 // and an h-proportional proposal one 64-byte record that also holds the vertex records
 // of its two candidates.  Optional eRJS boards (split bound, member board; extensions of
 // Section 3.3) cut the expected trials; see walk_kernel.
+#include <algorithm>
+
 #include "fw_device.h"
 #include "fw_internal.h"
 
@@ -571,6 +573,7 @@ walk_kernel(WalkArgs a)
     int32_t *lds = lds_all + (RO ? 0 : kWavesPerBlock * 4 * kWave * 4) + (threadIdx.x / kWave) * a.lds_cap;
     const int lane = lane_id();
     const uint64_t below = lanes_below(lane);
+    const uint64_t mine = ~0ull >> (kWave - a.wave_lanes);  // lanes that take walkers (1 <= wave_lanes <= 64)
 
     int mode = kIdle;
     int32_t q = 0;     // query of the lane's walker
@@ -608,8 +611,10 @@ walk_kernel(WalkArgs a)
         if (STATS && __ballot((st[kStTrials] | st[kStTriggers] | st[kStSteps]) > 0x40000000u) != 0)
             flush_stats(a, st, st_bytes);
 
-        // 1. hand walkers to idle lanes: one atomic per wave
-        const uint64_t idle = __ballot(mode == kIdle);
+        // 1. hand walkers to idle lanes: one atomic per wave.  Only the wave's first wave_lanes
+        //    lanes take walkers: a launch of fewer walkers than the grid has lanes spreads them
+        //    over all its waves, since a wave serves its lanes' eRVS steps one after another.
+        const uint64_t idle = __ballot(mode == kIdle) & mine;
         if (idle != 0 && !exhausted) {
             const int leader = __ffsll((unsigned long long)idle) - 1;
             const int cnt = __popcll(idle);
@@ -617,7 +622,7 @@ walk_kernel(WalkArgs a)
             if (lane == leader) first = atomicAdd(a.queue, (unsigned long long)cnt);
             first = (unsigned long long)bcast_i64((int64_t)first, leader);
             if ((int64_t)first + cnt >= a.n) exhausted = true;
-            if (mode == kIdle) {
+            if ((idle >> lane) & 1) {
                 const int64_t w = (int64_t)first + __popcll(idle & below);
                 if (w < a.n) {
                     const int32_t wq = BATCH ? query_of(a, w) : 0;
@@ -1850,8 +1855,11 @@ static hipError_t launch_walk_b(const WalkArgs &a, int kind, bool weighted, int 
                     : launch_walk_t<kMetaPath, false, BATCH>(a, grid, s);
 }
 
-hipError_t launch_walk(const WalkArgs &a, int kind, bool weighted, bool batch, int grid, hipStream_t s)
+hipError_t launch_walk(const WalkArgs &args, int kind, bool weighted, bool batch, int grid, hipStream_t s)
 {
+    WalkArgs a = args;
+    const int64_t waves = (int64_t)grid * kWavesPerBlock;
+    a.wave_lanes = (int32_t)std::min<int64_t>(kWave, (a.n + waves - 1) / waves);
     return batch ? launch_walk_b<true>(a, kind, weighted, grid, s) : launch_walk_b<false>(a, kind, weighted, grid, s);
 }
 
@@ -1887,7 +1895,8 @@ int walk_grid(int kind, bool weighted, bool batch, int lds_cap, int64_t n, bool 
                          : (rvs_only ? occupancy_b<false, true>(kind, weighted, lds_cap)
                                      : occupancy_b<false, false>(kind, weighted, lds_cap));
     int64_t grid = (int64_t)nb * cus;
-    const int64_t need = (n + kBlock - 1) / kBlock;
+    // never more waves than walkers (a launch of few walkers gets one lane or a few per wave)
+    const int64_t need = (n + kWavesPerBlock - 1) / kWavesPerBlock;
     if (grid > need) grid = need;
     return (int)(grid > 0 ? grid : 1);
 }
