@@ -20,7 +20,8 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_HBM_GBS = 8000.0
-KERNEL_SOURCES = ("paper_2512_00705_amd/csrc/fw_kernels.hip", "paper_2512_00705_amd/csrc/fw_device.h",
+KERNEL_SOURCES = ("paper_2512_00705_amd/csrc/fw_trial.h", "paper_2512_00705_amd/csrc/fw_walk.h",
+                  "paper_2512_00705_amd/csrc/fw_rvs.hip", "paper_2512_00705_amd/csrc/fw_device.h",
                   "paper_2512_00705_amd/csrc/fw_internal.h")
 TRAFFIC_FILE = "profiles/traffic_walk_kernel_node2vec_rmat22.txt"
 

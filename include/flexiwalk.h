@@ -196,8 +196,8 @@ int fw_graph_preprocess(fw_graph *g, void *stream);
 /* Copy h_MAX and h_SUM (nv floats each, host pointers) back to the host; synchronous. */
 int fw_graph_export_aux(const fw_graph *g, float *hmax, float *hsum);
 
-/* Build the edge index: an exact hash map of the entries (v, u) to h(v, u) (128-byte
- * buckets of eight 64-bit keys and their eight float h, at most half full; 32 bytes of
+/* Build the edge index: an exact hash map of the entries (v, u) to h(v, u) (64-byte
+ * buckets of five 64-bit keys and their five float h, at most half full; 25.6 bytes of
  * device memory per entry, rounded up to a power-of-two bucket count).  The membership
  * test u in N(prev) of an eRJS proposal (Node2Vec, second-order PageRank) then reads one
  * bucket instead of searching prev's sorted row, and so does a member-board trial's
@@ -288,7 +288,7 @@ int fw_plan_profile(fw_graph *g, const fw_logic *logic, fw_plan *out, void *stre
  * {256, 512, 1024, 2048, 4096}), the eRJS trial cap
  * rjs_cap in {16, 64, 256, 1024, 4096}, the lanes' shared eRVS threshold (rvs_share,
  * taken only when 2 % faster), the eRVS lanes on long rows (hub_lanes 128 or
- * 256 from hub_deg 1024 or 8192; fw_plan_autotune only, never for a mix) and the
+ * 256 from hub_deg 1024 or 8192, likewise; fw_plan_autotune only, never for a mix) and the
  * persistent grid (the occupancy limit, half of it, twice it); the fastest plan is
  * returned.  Every candidate
  * samples the same distribution; only the choice of kernel per step, and so the random

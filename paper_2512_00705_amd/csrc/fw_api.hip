@@ -45,6 +45,7 @@ int ok()
 using fw::host::check_logic;
 using fw::host::check_bound;
 using fw::host::check_plan;
+using fw::host::ev_of;
 using fw::host::fail;
 using fw::host::fill_args;
 using fw::host::fill_query;
@@ -73,7 +74,8 @@ static void graph_free(fw_graph *g)
 template <typename T>
 static int dev_copy(T **dst, const T *src, int64_t count, int on_device)
 {
-    const size_t bytes = sizeof(T) * (size_t)(count > 0 ? count : 1);
+    // whole 16-byte parts: the walk reads single entries of col in aligned parts of 16 bytes
+    const size_t bytes = (sizeof(T) * (size_t)(count > 0 ? count : 1) + 15) / 16 * 16;
     if (hipMalloc((void **)dst, bytes) != hipSuccess) {
         *dst = nullptr;
         return fail(FW_E_NOMEM, "hipMalloc of %zu bytes failed", bytes);
@@ -139,11 +141,13 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     }
     const bool packed = g->q8 && g->nv <= ((int64_t)1 << 24);
     const bool wide = g->ne >= ((int64_t)1 << 32);
-    if ((packed && hipMalloc((void **)&g->erec8, sizeof(uint32_t) * (size_t)(g->ne > 0 ? g->ne : 1)) != hipSuccess) ||
-        (!packed && hipMalloc((void **)&g->edges, sizeof(uint2) * (size_t)(g->ne > 0 ? g->ne : 1)) != hipSuccess) ||
+    // (edge records in whole 16-byte parts, as the walk reads them)
+    const size_t parts4 = ((size_t)g->ne + 3) / 4 + 1, parts2 = ((size_t)g->ne + 1) / 2 + 1;
+    if ((packed && hipMalloc((void **)&g->erec8, 16 * parts4) != hipSuccess) ||
+        (!packed && hipMalloc((void **)&g->edges, 16 * parts2) != hipSuccess) ||
         hipMalloc((void **)&g->vrec, sizeof(uint4) * (size_t)(g->nv > 0 ? g->nv : 1)) != hipSuccess ||
         (wide && hipMalloc((void **)&g->start_hi, sizeof(uint32_t) * (size_t)g->nv) != hipSuccess) ||
-        hipMalloc((void **)&g->scratch, 4 * sizeof(unsigned long long)) != hipSuccess) {
+        hipMalloc((void **)&g->scratch, (4 + fw::kQueueWords) * sizeof(unsigned long long)) != hipSuccess) {
         graph_free(g);
         return fail(FW_E_NOMEM, "fw_graph_create: hipMalloc failed");
     }
@@ -187,7 +191,7 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     g->symmetric = (host_chk[0] & 16u) == 0;
     e = fw::launch_layout(g->row_ptr, g->col, g->h, g->nv, g->ne, g->edges, g->vrec, g->start_hi, nullptr);
     if (e == hipSuccess && packed) e = fw::launch_pack8(g->col, (const uint8_t *)codes.p, g->ne, g->erec8, nullptr);
-    if (e == hipSuccess) e = hipMemset(g->scratch, 0, 4 * sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipMemset(g->scratch, 0, (4 + fw::kQueueWords) * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipDeviceSynchronize();
     if (e != hipSuccess) {
         graph_free(g);
@@ -217,15 +221,16 @@ int fw_graph_build_index(fw_graph *g, void *stream)
     if (!g) return fail(FW_E_INVALID, "fw_graph_build_index: null graph");
     if (g->mtab) return ok();
     HIP_TRY(hipSetDevice(g->device));
-    // power-of-two count of 128-byte buckets with at least 16 slots per 8 keys (load <= 1/2)
+    // power-of-two count of buckets, at most half the slots used
+    const uint64_t bucket_bytes = 16 * fw::kIndexBucketU4;
     uint64_t buckets = 1;
-    while (buckets * 8 < 2 * (uint64_t)g->ne) buckets <<= 1;
+    while (buckets * fw::kIndexSlots < 2 * (uint64_t)g->ne) buckets <<= 1;
     unsigned long long *tab = nullptr;
-    if (hipMalloc((void **)&tab, buckets * 128) != hipSuccess)
+    if (hipMalloc((void **)&tab, buckets * bucket_bytes) != hipSuccess)
         return fail(FW_E_NOMEM, "fw_graph_build_index: hipMalloc of %llu bytes failed",
-                    (unsigned long long)(buckets * 128));
+                    (unsigned long long)(buckets * bucket_bytes));
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = hipMemsetAsync(tab, 0xFF, buckets * 128, s);  // every key kEmptyKey
+    hipError_t e = hipMemsetAsync(tab, 0xFF, buckets * bucket_bytes, s);  // every key kEmptyKey
     if (e == hipSuccess) e = fw::launch_build_index(g->row_ptr, g->col, g->h, g->nv, tab, buckets - 1, s);
     if (e != hipSuccess) {
         (void)hipFree(tab);
@@ -447,6 +452,28 @@ void fw::host::plan_args(const fw_plan *pl, int32_t strategy, fw::WalkArgs &a)
     a.rvs_share = pl->rvs_share;
 }
 
+int fw::host::ev_of(const fw_plan *pl, int32_t strategy, const fw_logic *lg)
+{
+    if (pl->hub_deg > 0 && pl->hub_lanes > 64) return fw::kEvHub;
+    if (pl->rjs_cap < 64) return fw::kEvHot;  // steps that reach the trial cap go to eRVS
+    if (strategy == FW_RJS_ONLY) return fw::kEvNone;
+    if (strategy != FW_AUTO || pl->d_lo > 1) return fw::kEvHot;
+    // Eq. (runtime) sends a step to eRJS iff rho * (board area) < deg * S^, S^ = mean(w) * h_SUM
+    // (or the same over deg); the area is at most deg * max(w) * h_MAX or max(w) * h_SUM, and
+    // h_MAX <= h_SUM, so rho * max(w) < mean(w) decides every step with h_SUM > 0.  max / mean
+    // is 1 at step 0, for second-order PageRank at most 2, for MetaPath 2 (label-conditioned:
+    // rho < deg).
+    float ratio = 2.0f;
+    if (lg->kind == FW_METAPATH && pl->proposal == 2) {
+        ratio = 1.0f;
+    } else if (lg->kind == FW_NODE2VEC) {
+        fw::QueryDev q;
+        fill_query(lg, q);
+        ratio = fmaxf(1.0f, q.wmax1 / q.wavg1);
+    }
+    return pl->rho * ratio < 1.0f ? fw::kEvNone : fw::kEvHot;
+}
+
 extern "C" {
 
 int fw_walk(fw_graph *g, const fw_logic *lg, const fw_plan *pl, int32_t strategy, const int32_t *starts, int64_t n,
@@ -472,7 +499,7 @@ int fw_walk(fw_graph *g, const fw_logic *lg, const fw_plan *pl, int32_t strategy
     plan_args(pl, strategy, a);
     a.n = n;
     a.stats = (unsigned long long *)stats;
-    a.queue = g->scratch;
+    a.queue = g->scratch + 4;
     a.err = (int *)(g->scratch + 1);
     a.q0.first = 0;
     a.q0.n = n;
@@ -483,11 +510,8 @@ int fw_walk(fw_graph *g, const fw_logic *lg, const fw_plan *pl, int32_t strategy
     a.q0.key0 = (uint32_t)seed;
     a.q0.key1 = (uint32_t)(seed >> 32);
     a.nq = 1;
-    const int grid =
-        pl->grid > 0 ? pl->grid : fw::walk_grid(lg->kind, weighted, false, a.lds_cap, n, strategy == FW_RVS_ONLY);
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(fw::launch_zero(g->scratch, 1, s));
-    HIP_TRY(fw::launch_walk(a, lg->kind, weighted, false, grid, s));
+    const fw::WalkShape w = fw::walk_shape(a, lg->kind, weighted, false, ev_of(pl, strategy, lg), n, pl->grid);
+    HIP_TRY(fw::launch_walk(a, w, (hipStream_t)stream));
     return ok();
 }
 
@@ -585,7 +609,8 @@ int fw_graph_build_label_alias(fw_graph *g, void *stream)
     const size_t rec = 16 * (size_t)fw::kPropU4;
     int64_t *lrow = nullptr;
     uint4 *lprop = nullptr;
-    if (hipMalloc((void **)&lrow, sizeof(int64_t) * (ng + 1)) != hipSuccess) {
+    // (whole 16-byte parts, as the walk reads them)
+    if (hipMalloc((void **)&lrow, 16 * (ng / 2 + 2)) != hipSuccess) {
         return fail(FW_E_NOMEM, "fw_graph_build_label_alias: hipMalloc of %zu bytes failed", 8 * (ng + 1));
     }
     if (hipMalloc((void **)&lprop, rec * ne) != hipSuccess) {
@@ -898,8 +923,10 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     }
     // eRVS lanes on long rows, for one logic only (hub lanes run in fw_walk launches; a mix
     // is tuned for the batches and servers that take it): P = 128 or 256 on rows of at
-    // least 1024 or 8192 entries
-    if (n_logics == 1) {
+    // least 1024 or 8192 entries; skipped where every step is eRJS, which they change nothing
+    // of, and taken only when clearly faster, since batches and servers refuse them
+    if (n_logics == 1 && ev_of(&bestp, FW_AUTO, &logics[0]) != fw::kEvNone) {
+        const float base = bestt;
         for (int32_t hl : {128, 256})
             for (int32_t hd : {1024, 8192}) {
                 fw_plan p = bestp;
@@ -907,7 +934,7 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
                 p.hub_lanes = hl;
                 float t;
                 if ((rc = time_plan(p, &t)) != FW_OK) return rc;
-                if (t < bestt) bestt = t, bestp = p;
+                if (t < bestt && t < 0.98f * base) bestt = t, bestp = p;
             }
     }
     // the persistent grid: the occupancy limit (0), half of it, and twice it (blocks past
@@ -915,7 +942,12 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     {
         int64_t nw = 0;
         for (int32_t i = 0; i < n_logics; ++i) nw += n;
-        const int full = fw::walk_grid(logics[0].kind, logics[0].weighted && g->h, batched, bestp.lds_cap, nw);
+        fw::WalkArgs a;
+        fill_args(g, &logics[0], a);
+        plan_args(&bestp, FW_AUTO, a);
+        int ev = ev_of(&bestp, FW_AUTO, &logics[0]);
+        for (int32_t i = 1; i < n_logics; ++i) ev = std::max(ev, ev_of(&bestp, FW_AUTO, &logics[i]));
+        const int full = fw::walk_shape(a, logics[0].kind, logics[0].weighted && g->h, batched, ev, nw, 0).grid;
         for (int gr : {full / 2, full * 2}) {
             if (gr < 1) continue;
             fw_plan p = bestp;
@@ -932,9 +964,7 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
 struct fw_batch {
     fw_graph *g = nullptr;
     fw::WalkArgs a;
-    int kind = 0;
-    bool weighted = false;
-    int grid = 1;
+    fw::WalkShape shape{};
     fw::QueryDev *d_queries = nullptr;
     unsigned long long *d_queue = nullptr;
     hipGraph_t graph = nullptr;
@@ -1011,7 +1041,7 @@ int fw_batch_create(fw_graph *g, const fw_query *qs, int64_t nq, const fw_plan *
     fw_batch *b = new fw_batch();
     b->g = g;
     if (hipMalloc((void **)&b->d_queries, sizeof(fw::QueryDev) * tab.size()) != hipSuccess ||
-        hipMalloc((void **)&b->d_queue, sizeof(unsigned long long)) != hipSuccess) {
+        hipMalloc((void **)&b->d_queue, fw::kQueueWords * sizeof(unsigned long long)) != hipSuccess) {
         batch_free(b);
         return fail(FW_E_NOMEM, "fw_batch_create: hipMalloc failed");
     }
@@ -1027,9 +1057,9 @@ int fw_batch_create(fw_graph *g, const fw_query *qs, int64_t nq, const fw_plan *
     b->a.err = (int *)(g->scratch + 1);
     b->a.queries = b->d_queries;
     b->a.nq = (int32_t)nq;
-    b->kind = nq > 0 ? qs[0].logic.kind : FW_NODE2VEC;
-    b->weighted = weighted;
-    b->grid = pl->grid > 0 ? pl->grid : fw::walk_grid(b->kind, weighted, true, pl->lds_cap, total);
+    int ev = fw::kEvNone;
+    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(pl, strategy, &qs[i].logic));
+    b->shape = fw::walk_shape(b->a, nq > 0 ? qs[0].logic.kind : FW_NODE2VEC, weighted, true, ev, total, pl->grid);
     *out = b;
     return ok();
 }
@@ -1040,9 +1070,7 @@ int fw_batch_launch(fw_batch *b, uint64_t *stats, void *stream)
     if (b->a.n == 0) return ok();
     fw::WalkArgs a = b->a;
     a.stats = (unsigned long long *)stats;
-    hipStream_t s = (hipStream_t)stream;
-    HIP_TRY(fw::launch_zero(b->d_queue, 1, s));
-    HIP_TRY(fw::launch_walk(a, b->kind, b->weighted, true, b->grid, s));
+    HIP_TRY(fw::launch_walk(a, b->shape, (hipStream_t)stream));
     return ok();
 }
 
@@ -1174,9 +1202,9 @@ int fw_batch_run_noalloc(fw_graph *g, const fw_query *qs, int64_t nq, const fw_p
     a.err = (int *)(g->scratch + 1);
     a.queries = tab;
     a.nq = (int32_t)nq;
-    const int grid = pl->grid > 0 ? pl->grid : fw::walk_grid(qs[0].logic.kind, weighted, true, pl->lds_cap, total);
-    HIP_TRY(fw::launch_zero(queue, 1, s));
-    HIP_TRY(fw::launch_walk(a, qs[0].logic.kind, weighted, true, grid, s));
+    int ev = fw::kEvNone;
+    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(pl, strategy, &qs[i].logic));
+    HIP_TRY(fw::launch_walk(a, fw::walk_shape(a, qs[0].logic.kind, weighted, true, ev, total, pl->grid), s));
     return ok();
 }
 

@@ -147,6 +147,11 @@ __device__ __forceinline__ uint32_t bcast_u32(uint32_t v, int src)
     return (uint32_t)__builtin_amdgcn_readlane((int)v, src);
 }
 
+__device__ __forceinline__ float bcast_f32(float v, int src)
+{
+    return __uint_as_float(bcast_u32(__float_as_uint(v), src));
+}
+
 __device__ __forceinline__ int64_t bcast_i64(int64_t v, int src)
 {
     const uint32_t lo = bcast_u32((uint32_t)(uint64_t)v, src);
@@ -269,14 +274,16 @@ __device__ __forceinline__ bool sorted_contains_interp(const int32_t *a, int32_t
     return sorted_find_interp(a, n, u, vend) >= 0;
 }
 
-// Exact map of the graph's entries (v, u) to their h: open addressing over 128-byte
-// buckets (one DRAM line) of eight 64-bit keys v << 32 | u followed by their eight h
-// values, the first bucket chosen by the SplitMix64 finaliser (Steele, Lea, Flood,
-// OOPSLA'14), then linear probing bucket by bucket.  At most half the slots are used, so
-// a query almost always reads one bucket: one memory request where a search of the
-// sorted row needs several dependent ones.
+// Exact map of the graph's entries (v, u) to their h: open addressing over 64-byte buckets
+// (half a DRAM line) of five 64-bit keys v << 32 | u followed by their five h values, the
+// first bucket chosen by the SplitMix64 finaliser (Steele, Lea, Flood, OOPSLA'14), then
+// linear probing bucket by bucket.  At most half the slots are used, so a query almost always
+// reads one bucket: one memory request where a search of the sorted row needs several
+// dependent ones.  A bucket fits the walk's 64-byte reads (of eight keys and eight h, 96 of
+// 128 bytes, a lookup with its h took six requests of 16 bytes).
 constexpr unsigned long long kEmptyKey = ~0ull;
-constexpr int kIndexBucketU4 = 8;  // uint4 per bucket: keys in parts 0..3, h in parts 4..5
+constexpr int kIndexBucketU4 = 4;  // uint4 per bucket: words 0..9 the keys, 10..14 the h, 15 unused
+constexpr int kIndexSlots = 5;
 
 __device__ __forceinline__ uint64_t mix64(uint64_t z)
 {
@@ -290,41 +297,45 @@ __device__ __forceinline__ uint64_t edge_key(int32_t v, int32_t u)
     return ((uint64_t)(uint32_t)v << 32) | (uint64_t)(uint32_t)u;
 }
 
-// tab: kIndexBucketU4 uint4 per bucket, mask = buckets - 1 (buckets a power of two).  The
-// key parts of a bucket are loaded before any is tested, so they go out together as one
-// request instead of one dependent load after another.  Scans at most every bucket
-// once, so it ends even on a full table.  Returns the slot of (v, u) in [0, 8), or -1.
-// With H the hit's h is read from the bucket's h part (the same DRAM line, so a cache
-// hit) and stored in *h.
-template <bool H>
-__device__ __forceinline__ int index_probe(const uint4 *tab, uint64_t mask, int32_t v, int32_t u, float *h)
+// The bucket y0..y3: whether it holds `key` (its h in `h` then), and whether it has an empty slot.
+__device__ __forceinline__ bool index_match(uint4 y0, uint4 y1, uint4 y2, uint4 y3, uint64_t key, float &h, bool &empty)
+{
+    const uint64_t k0 = ((uint64_t)y0.y << 32) | y0.x, k1 = ((uint64_t)y0.w << 32) | y0.z;
+    const uint64_t k2 = ((uint64_t)y1.y << 32) | y1.x, k3 = ((uint64_t)y1.w << 32) | y1.z;
+    const uint64_t k4 = ((uint64_t)y2.y << 32) | y2.x;
+    // slots fill from the first on
+    empty = k4 == kEmptyKey;
+    uint32_t hb = y2.z;
+    bool found = k0 == key;
+    if (k1 == key) found = true, hb = y2.w;
+    if (k2 == key) found = true, hb = y3.x;
+    if (k3 == key) found = true, hb = y3.y;
+    if (k4 == key) found = true, hb = y3.z;
+    h = __uint_as_float(hb);
+    return found;
+}
+
+// tab: kIndexBucketU4 uint4 per bucket, mask = buckets - 1 (buckets a power of two).  Scans at
+// most every bucket once, so it ends even on a full table.  Returns whether (v, u) is there, its
+// h in `h` then.
+__device__ __forceinline__ bool index_find(const uint4 *tab, uint64_t mask, int32_t v, int32_t u, float &h)
 {
     const uint64_t key = edge_key(v, u);
     uint64_t b = mix64(key) & mask;
     for (uint64_t t = 0; t <= mask; ++t) {
         const uint4 *p = tab + b * kIndexBucketU4;
-        const uint4 x[4] = {p[0], p[1], p[2], p[3]};
-        int slot = -1;
-        bool empty = false;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint64_t k0 = ((uint64_t)x[i].y << 32) | x[i].x, k1 = ((uint64_t)x[i].w << 32) | x[i].z;
-            slot = k0 == key ? 2 * i : (k1 == key ? 2 * i + 1 : slot);
-            empty = empty || k0 == kEmptyKey || k1 == kEmptyKey;
-        }
-        if (slot >= 0) {
-            if (H) *h = reinterpret_cast<const float *>(p + 4)[slot];
-            return slot;
-        }
-        if (empty) return -1;
+        bool empty;
+        if (index_match(p[0], p[1], p[2], p[3], key, h, empty)) return true;
+        if (empty) return false;
         b = (b + 1) & mask;
     }
-    return -1;
+    return false;
 }
 
 __device__ __forceinline__ bool index_contains(const uint4 *tab, uint64_t mask, int32_t v, int32_t u)
 {
-    return index_probe<false>(tab, mask, v, u, nullptr) >= 0;
+    float h;
+    return index_find(tab, mask, v, u, h);
 }
 
 // ceil(log2(m + 1)): probes of a binary search over m entries.

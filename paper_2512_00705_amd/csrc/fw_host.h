@@ -22,10 +22,10 @@ struct fw_graph {
     bool q8 = false;                        // the weights came as 8-bit codes
     uint4 *vrec = nullptr;                  // {start_lo, degree, bits(h_MAX), bits(h_SUM)} per vertex
     uint32_t *start_hi = nullptr;           // high row-start bits, only when ne >= 2^32
-    unsigned long long *scratch = nullptr;  // [0] walker queue, [1] error flag (int)
+    unsigned long long *scratch = nullptr;  // [1] error flag (int), [4..] walker queue (kQueueWords)
     bool prepped = false;
     bool symmetric = false;                 // every (v, u) has a reverse (u, v) with equal h
-    unsigned long long *mtab = nullptr;     // edge index: 128-byte buckets of 8 keys v << 32 | u and their h, or null
+    unsigned long long *mtab = nullptr;     // edge index: 64-byte buckets of 5 keys v << 32 | u and their h, or null
     uint4 *prop = nullptr;                  // h-proportional proposal records (kPropU4 uint4 per entry), or null
     int64_t *lrow = nullptr;                // label groups: first grouped position of (v, l) at v * nlab + l, or null
     uint4 *lprop = nullptr;                 // proposal records of the label groups (grouped order), or null
@@ -52,6 +52,9 @@ void fill_query(const fw_logic *lg, QueryDev &q);
 // Graph fields and logic-derived fields of a launch.
 void fill_args(const fw_graph *g, const fw_logic *lg, WalkArgs &a);
 void plan_args(const fw_plan *pl, int32_t strategy, WalkArgs &a);
+// How walk_kernel keeps eRVS for this plan, strategy and logic (Ev): kEvNone when every
+// step at a vertex with some weight goes to eRJS.
+int ev_of(const fw_plan *pl, int32_t strategy, const fw_logic *lg);
 
 }  // namespace host
 }  // namespace fw

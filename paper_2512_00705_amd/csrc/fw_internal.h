@@ -34,17 +34,6 @@ constexpr int kBlock = 256;          // 4 wavefronts per block, each independent
 constexpr int kWavesPerBlock = kBlock / 64;
 constexpr int kDefaultLdsCap = 512;  // int32 entries of N(prev) per wavefront: with the four 1 KB vertex-record
                                      // slots a block takes 24 KB, six blocks per CU (1024: 32 KB blocks, slower)
-// eRJS proposals whose loads a lane issues together.  Only depth 3 is built: a build with
-// depth 4 whose counted launches were compiled for 5 waves per SIMD (heavy spills) left the
-// oracle's path after eRJS cap fall-backs, and that failure has no identified cause, so no
-// other depth may be built until one is found.
-#ifndef FW_RJS_BATCH
-#define FW_RJS_BATCH 3
-#endif
-#if FW_RJS_BATCH != 3
-#error "FW_RJS_BATCH: only the eRJS load batch of depth 3 has passed the parity suite"
-#endif
-constexpr int kRjsBatch = FW_RJS_BATCH;
 // h-proportional proposal record per CSR entry, 64 bytes (one DRAM line holds it whole):
 //   {col_k, bits(h_k), col_a, bits(h_a)}, {threshold, label_k | label_a << 8, 0, 0},
 //   vrec[col_k], vrec[col_a]  (the candidates' vertex records for the next step's set-up)
@@ -53,24 +42,18 @@ constexpr int kPropU4 = 4;
 #define FW_MERGE_RATIO 8
 #endif
 constexpr int kMergeRatio = FW_MERGE_RATIO;  // eRVS merges N(v) with N(prev) while d(prev) <= this * d(v)
-#ifndef FW_MIN_WAVES
-#define FW_MIN_WAVES 5
-#endif
-#ifndef FW_MIN_WAVES_BATCH
-#define FW_MIN_WAVES_BATCH 4
-#endif
-// resident waves per SIMD the walk kernel is compiled for: single-query launches at 5 (96
-// VGPRs; the extra wave hides more memory latency than the few spills cost), batched and
-// resumable ones at 4 (their per-query state spills more at 96).  Launches that keep the
-// device counters are compiled for 4 waves, fixed: their extra state spills heavily at 96,
-// and the one build that did so is the unexplained parity failure noted at kRjsBatch (the
-// persistent grid is sized by the counter-free variant; blocks beyond what is resident
-// start late and find the walker queue drained)
-constexpr int kMinWaves = FW_MIN_WAVES;
-constexpr int kMinWavesBatch = FW_MIN_WAVES_BATCH;
+// resident waves per SIMD rvs_kernel is compiled for: 7 without the device counters (no
+// spills), 4 with them or with hub lanes (their extra lane state)
 constexpr int kMinWavesCounted = 4;
-// the eRVS-only variant (no eRJS code) fits 6 waves in its registers without spills
 constexpr int kMinWavesRvsOnly = 7;
+
+// How walk_kernel keeps eRVS: kEvNone for plans that send every ordinary step to eRJS (no scan
+// in the kernel, so no registers for it; a walk that does meet an eRVS step is parked and run
+// on by a kEvHot launch), kEvHot otherwise, kEvHub with hub lanes (P = 128 or 256 on long rows).
+enum Ev : int { kEvNone = 0, kEvHot = 1, kEvHub = 2 };
+
+constexpr int kHotWaves = 4;    // resident waves per SIMD of the kEvHot form
+constexpr int kQueueWords = 4;  // walker counter, parked flag, the resuming launch's counter, unused
 
 // Per-query constants of a walk job.  Float constants are prepared on the host in float32
 // exactly as the definition states, so every float32 evaluation agrees bit for bit.
@@ -120,6 +103,8 @@ struct WalkArgs {
     int64_t n;                  // walkers in the launch (all queries)
     unsigned long long *stats;  // may be null
     unsigned long long *queue;  // next walker to hand out
+    int *parked;                // set to 1 when a walk was parked for the kEvHot launch that follows
+    int32_t resume;             // that launch: take only the parked walks (lengths[i] = -1 - step)
     int *err;                   // set to 1 on an out-of-range start
     float rho;
     int32_t d_lo;
@@ -128,9 +113,12 @@ struct WalkArgs {
     int32_t lds_cap;
     int32_t item_bytes;         // col (+ h) (+ label) per scanned or proposed edge
     int32_t wave_lanes;         // lanes of each wave that take walkers (set by launch_walk from n and the grid)
+    // walk_kernel (set by launch_walk): the first static_n walkers are shared out over the first
+    // static_waves waves, static_each to each and one more to the first static_more
+    int64_t static_n, static_waves, static_each, static_more;
     int32_t tick_steps;         // resumable walks: steps per walker per launch
     int32_t bound;              // 1: Node2Vec split eRJS bound (symmetric graphs only)
-    const uint4 *mtab;          // edge index (8 uint4 per bucket) or null: search the sorted rows
+    const uint4 *mtab;          // edge index (kIndexBucketU4 uint4 per bucket) or null: search the sorted rows
     const uint4 *prop;          // proposal records (kPropU4 uint4 per entry) or null
     int32_t proposal;           // 1: h-proportional eRJS proposals through `prop`; 2: as 1, and
                                 // MetaPath proposes within the wanted label's group (`lprop`)
@@ -147,7 +135,28 @@ struct WalkArgs {
     int32_t nq;
 };
 
-hipError_t launch_walk(const WalkArgs &a, int kind, bool weighted, bool batch, int grid, hipStream_t s);
+// What a walk launch runs: the logic, a batch's form or one query's, how it keeps eRVS, its
+// persistent grid and how many of the grid's blocks are resident at once.
+struct WalkShape {
+    int kind;
+    bool weighted, batch;
+    int ev;
+    int grid, resident;
+};
+// The shape of a launch of n walkers: the plan's grid, or (0) blocks that fill the device, at
+// most one wave per walker.  `ev` as the plan has it; a.stats and a.tick_steps tell whether the
+// launch counts or resumes.
+WalkShape walk_shape(const WalkArgs &a, int kind, bool weighted, bool batch, int ev, int64_t n, int plan_grid);
+// One walk launch (the walker counter cleared first when it is needed).  Launches with strategy
+// kRvsOnly of one query take rvs_kernel, all others walk_kernel.  a.queue points to kQueueWords
+// words.
+hipError_t launch_walk(const WalkArgs &a, const WalkShape &w, hipStream_t s);
+hipError_t launch_trial_node2vec(const WalkArgs &a, bool weighted, bool batch, int ev, int grid, hipStream_t s);
+hipError_t launch_trial_secondpr(const WalkArgs &a, bool weighted, bool batch, int ev, int grid, hipStream_t s);
+hipError_t launch_trial_metapath(const WalkArgs &a, bool weighted, bool batch, int ev, int grid, hipStream_t s);
+int trial_blocks_node2vec(bool weighted, bool batch, int proposal, int ev, int lds_cap);
+int trial_blocks_secondpr(bool weighted, bool batch, int proposal, int ev, int lds_cap);
+int trial_blocks_metapath(bool weighted, bool batch, int proposal, int ev, int lds_cap);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
 hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 // 8-bit weights: h[k] = h_scale * code[k] (float32 product) for k < ne.
@@ -183,8 +192,8 @@ hipError_t launch_label_groups(const int64_t *row_ptr, const int32_t *col, const
 // thr[k] = threshold and alias[k] = alias offset of proposal record k, for k < ne.
 hipError_t launch_export_alias(const uint4 *prop, int64_t ne, uint32_t *thr, int32_t *alias, hipStream_t s);
 // Edge index: inserts every entry (v, col[k]) of the rows with its h (1 when h is null) into
-// `tab` (buckets of 8 keys and 8 h, 128 bytes each, keys all kEmptyKey on entry;
-// buckets = mask + 1, a power of two, at least a quarter of ne).
+// `tab` (buckets of kIndexSlots keys and h, 64 bytes each, keys all kEmptyKey on entry;
+// buckets = mask + 1, a power of two, with at least twice as many slots as entries).
 hipError_t launch_build_index(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv,
                               unsigned long long *tab, uint64_t mask, hipStream_t s);
 // blocks * kBlock lanes each read 4 * rounds random 8-byte records of a[0, mask] (mask + 1 a
@@ -201,9 +210,5 @@ hipError_t launch_profile(const WalkArgs &a, int kind, bool weighted, bool rjs_s
                           int nsample, int per_node, float *sink, hipStream_t s);
 // {vertex k * stride, its degree} for k < n (stride * (n - 1) < nv).
 hipError_t launch_profile_pick(const int64_t *row_ptr, int64_t stride, int n, int2 *out, hipStream_t s);
-// Persistent grid filling the device: resident blocks per CU (of the counter-free kernel
-// variant the launch takes: batched, eRVS-only (strategy FW_RVS_ONLY, single query) or the
-// general one) times the CUs, at most one wave per walker.
-int walk_grid(int kind, bool weighted, bool batch, int lds_cap, int64_t n, bool rvs_only = false);
 
 }  // namespace fw

@@ -228,6 +228,7 @@ int tick(fw_server *s)
         fw::QueryDev *tab = s->h_table + (size_t)grp * s->max_active;
         int32_t nq = 0;
         int64_t total = 0;
+        int ev = fw::kEvNone;
         const fw_logic *lg0 = nullptr;
         for (Request *r : s->active) {
             if (r->logic.kind != kind || (r->logic.weighted != 0) != weighted_logic) continue;
@@ -245,6 +246,7 @@ int tick(fw_server *s)
             d.key1 = (uint32_t)(r->seed >> 32);
             total += r->n;
             lg0 = &r->logic;
+            ev = std::max(ev, fw::host::ev_of(&s->plan, s->strategy, lg0));
         }
         if (total == 0) continue;
         fw::QueryDev *dtab = s->d_table + (size_t)grp * s->max_active;
@@ -260,9 +262,7 @@ int tick(fw_server *s)
         a.nq = nq;
         a.tick_steps = s->tick_steps;
         const bool weighted = weighted_logic && s->g->h;
-        const int grid = s->plan.grid > 0 ? s->plan.grid : fw::walk_grid(kind, weighted, true, a.lds_cap, total);
-        SRV_TRY(fw::launch_zero(s->d_queue + grp, 1, s->stream));
-        SRV_TRY(fw::launch_walk(a, kind, weighted, true, grid, s->stream));
+        SRV_TRY(fw::launch_walk(a, fw::walk_shape(a, kind, weighted, true, ev, total, s->plan.grid), s->stream));
     }
     SRV_TRY(hipMemcpyAsync(s->h_done, s->d_done, sizeof(int32_t) * (size_t)s->max_active, hipMemcpyDeviceToHost,
                            s->stream));
