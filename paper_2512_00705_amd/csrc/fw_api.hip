@@ -153,10 +153,13 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     }
 
     // validate on the device: row pointers first (they bound every later access)
-    unsigned long long *chk = g->scratch;  // [0] error bits, [1] max degree
+    // [0] error bits, [1] max degree, [2] entries that do not ascend, [3] those that start a row,
+    // [4] entries with a smaller neighbour less those with a greater one
+    unsigned long long *chk = g->scratch;
     int host_err = 0;
-    unsigned long long host_chk[2] = {0, 0};
-    hipError_t e = hipMemset(chk, 0, 2 * sizeof(unsigned long long));
+    unsigned long long host_chk[5] = {};
+    static_assert(4 + fw::kQueueWords >= 5, "the scratch words hold the checks");
+    hipError_t e = hipMemset(chk, 0, sizeof(host_chk));
     if (e == hipSuccess) e = fw::launch_validate_rows(g->row_ptr, g->nv, g->ne, (int *)chk, nullptr);
     if (e == hipSuccess) e = hipMemcpy(host_chk, chk, sizeof(host_chk), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {
@@ -168,27 +171,27 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
         graph_free(g);
         return fail(FW_E_INVALID, "fw_graph_create: row_ptr must start at 0, end at ne and not decrease");
     }
-    e = fw::launch_validate_edges(g->row_ptr, g->col, g->h, g->nv, (int *)chk, chk + 1, nullptr);
+    e = fw::launch_validate_edges(g->row_ptr, g->col, g->h, g->nv, g->ne, (int *)chk, chk + 1, chk + 2, nullptr);
     if (e == hipSuccess) e = hipMemcpy(host_chk, chk, sizeof(host_chk), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {
         graph_free(g);
         return fail(FW_E_DEVICE, "fw_graph_create: %s", hipGetErrorString(e));
     }
     host_err = (int)(host_chk[0] & 0xffffffffu);
-    if (host_err != 0) {
+    if (host_err != 0 || host_chk[2] != host_chk[3]) {
         graph_free(g);
         return fail(FW_E_INVALID,
                     "fw_graph_create: col must be in [0, nv) and strictly ascending per row; h finite and >= 0");
     }
     g->max_deg = (int64_t)host_chk[1];
     // symmetry decides whether the split eRJS bound may be used; not an error
-    e = fw::launch_check_symmetry(g->row_ptr, g->col, g->h, g->nv, (int *)chk, nullptr);
+    e = fw::launch_check_symmetry(g->row_ptr, g->col, g->h, g->nv, g->ne, (int *)chk, chk + 4, nullptr);
     if (e == hipSuccess) e = hipMemcpy(host_chk, chk, sizeof(host_chk), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {
         graph_free(g);
         return fail(FW_E_DEVICE, "fw_graph_create: %s", hipGetErrorString(e));
     }
-    g->symmetric = (host_chk[0] & 16u) == 0;
+    g->symmetric = (host_chk[0] & 16u) == 0 && host_chk[4] == 0;
     e = fw::launch_layout(g->row_ptr, g->col, g->h, g->nv, g->ne, g->edges, g->vrec, g->start_hi, nullptr);
     if (e == hipSuccess && packed) e = fw::launch_pack8(g->col, (const uint8_t *)codes.p, g->ne, g->erec8, nullptr);
     if (e == hipSuccess) e = hipMemset(g->scratch, 0, (4 + fw::kQueueWords) * sizeof(unsigned long long));
@@ -231,7 +234,7 @@ int fw_graph_build_index(fw_graph *g, void *stream)
                     (unsigned long long)(buckets * bucket_bytes));
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemsetAsync(tab, 0xFF, buckets * bucket_bytes, s);  // every key kEmptyKey
-    if (e == hipSuccess) e = fw::launch_build_index(g->row_ptr, g->col, g->h, g->nv, tab, buckets - 1, s);
+    if (e == hipSuccess) e = fw::launch_build_index(g->row_ptr, g->col, g->h, g->nv, g->ne, tab, buckets - 1, s);
     if (e != hipSuccess) {
         (void)hipFree(tab);
         return fail(FW_E_DEVICE, "fw_graph_build_index: %s", hipGetErrorString(e));

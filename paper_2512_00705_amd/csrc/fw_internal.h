@@ -194,18 +194,20 @@ hipError_t launch_export_alias(const uint4 *prop, int64_t ne, uint32_t *thr, int
 // Edge index: inserts every entry (v, col[k]) of the rows with its h (1 when h is null) into
 // `tab` (buckets of kIndexSlots keys and h, 64 bytes each, keys all kEmptyKey on entry;
 // buckets = mask + 1, a power of two, with at least twice as many slots as entries).
-hipError_t launch_build_index(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv,
+hipError_t launch_build_index(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int64_t ne,
                               unsigned long long *tab, uint64_t mask, hipStream_t s);
 // blocks * kBlock lanes each read 4 * rounds random 8-byte records of a[0, mask] (mask + 1 a
 // power of two).
 hipError_t launch_random_reads(const uint2 *a, uint64_t mask, int blocks, int rounds, unsigned *sink, hipStream_t s);
-// Sets bit 4 of *err unless every entry (v, u) has a reverse (u, v) with the same h.
-// Rows must already be validated (in range, strictly ascending).
-hipError_t launch_check_symmetry(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int *err,
-                                 hipStream_t s);
+// Every entry (v, u) has a reverse (u, v) with the same h iff bit 4 of *err stays clear and
+// *balance (zero on entry) zero.  Rows must already be validated (in range, strictly ascending).
+hipError_t launch_check_symmetry(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int64_t ne,
+                                 int *err, unsigned long long *balance, hipStream_t s);
 hipError_t launch_validate_rows(const int64_t *row_ptr, int64_t nv, int64_t ne, int *err, hipStream_t s);
-hipError_t launch_validate_edges(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv,
-                                 int *err, unsigned long long *max_deg, hipStream_t s);
+// Sets bit 2 of *err when a neighbour is out of range or an h not finite and >= 0; the rows are
+// strictly ascending iff cnt[0] == cnt[1] (both zero on entry).  *max_deg: the longest row.
+hipError_t launch_validate_edges(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int64_t ne,
+                                 int *err, unsigned long long *max_deg, unsigned long long *cnt, hipStream_t s);
 hipError_t launch_profile(const WalkArgs &a, int kind, bool weighted, bool rjs_style, const int32_t *nodes,
                           int nsample, int per_node, float *sink, hipStream_t s);
 // {vertex k * stride, its degree} for k < n (stride * (n - 1) < nv).

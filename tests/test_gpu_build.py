@@ -1,0 +1,123 @@
+"""What creating a graph and building its tables read from it (needs an MI355X): rows that start,
+end and change anywhere among the 64 entries that a wave takes at a time, long runs of empty
+rows, rows much longer than the others.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests._gpu import GpuGraph, fw_logic, fw_plan, gpu_walk
+
+import paper_2512_00705_amd as fw
+
+pytestmark = pytest.mark.gpu
+
+
+def _rows(lens, nv, seed=3):
+    """Rows of the given lengths (the others empty) with random ascending neighbours."""
+    rng = np.random.default_rng(seed)
+    row_ptr = np.zeros(nv + 1, np.int64)
+    row_ptr[1 : 1 + len(lens)] = lens
+    row_ptr = np.cumsum(row_ptr)
+    col = np.concatenate([np.sort(rng.choice(nv, n, replace=False)) for n in lens] or [np.zeros(0)]).astype(np.int32)
+    h = rng.integers(1, 9, len(col)).astype(np.float32)
+    return {"nv": nv, "ne": len(col), "row_ptr": row_ptr, "col": col, "h": h}
+
+
+def _symmetric(leaves, gap):
+    """A star whose leaves lie `gap` vertices apart, and a path through them."""
+    ids = [gap * (i + 1) for i in range(leaves)]
+    edges = [(0, i) for i in ids] + [(ids[i], ids[i + 1]) for i in range(0, leaves - 1, 2)]
+    g = synth.csr_from_edges(ids[-1] + gap, edges)
+    src = np.repeat(np.arange(g["nv"]), np.diff(g["row_ptr"]))
+    lo, hi = np.minimum(src, g["col"]), np.maximum(src, g["col"])
+    g["h"] = (1 + (lo * 7 + hi * 13) % 5).astype(np.float32)
+    return g
+
+
+def _drop(g, k):
+    out = dict(g, ne=g["ne"] - 1, col=np.delete(g["col"], k), h=np.delete(g["h"], k), row_ptr=g["row_ptr"].copy())
+    out["row_ptr"][np.searchsorted(g["row_ptr"], k, side="right") :] -= 1
+    return out
+
+
+@pytest.mark.parametrize("leaves,gap", [(1, 1), (31, 1), (63, 3), (64, 1), (129, 70), (3000, 7), (500, 5000)])
+def test_symmetry_is_seen(leaves, gap):
+    """fw_graph_info's `symmetric` of a symmetric graph, of one that lacks one entry (the first, one
+    in the middle, the last) and of one with a different weight on one direction."""
+    g = _symmetric(leaves, gap)
+
+    def symmetric(x):
+        gg = GpuGraph(x, preprocess=False)
+        try:
+            return bool(fw.fw_graph_info(gg.handle)[3])
+        finally:
+            gg.close()
+
+    assert symmetric(g)
+    for k in {0, g["ne"] // 2, g["ne"] - 1}:
+        assert not symmetric(_drop(g, k))
+        h = g["h"].copy()
+        h[k] += 1
+        assert not symmetric(dict(g, h=h))
+
+
+def test_directed_cycle_is_not_symmetric():
+    g = synth.csr_from_edges(4, [(0, 1), (1, 2), (2, 3), (3, 0)], symmetric=False)
+    gg = GpuGraph(g, preprocess=False)
+    try:
+        assert not fw.fw_graph_info(gg.handle)[3]
+    finally:
+        gg.close()
+
+
+@pytest.mark.parametrize("at", [1, 63, 64, 65, 255, 256, 4095])
+def test_rows_must_ascend(at):
+    """Equal and falling neighbours are refused wherever they are; a fall at a row's start is none."""
+    g = _rows([at, 4096 - at, 40], 9000)
+    GpuGraph(g).close()
+    for k in (max(1, at - 1), at + 1, 4095 if at < 4094 else 4097):
+        if k in g["row_ptr"]:
+            continue
+        for c in (g["col"][k - 1], max(0, g["col"][k - 1] - 1)):
+            bad = g["col"].copy()
+            bad[k] = c
+            with pytest.raises(fw.FlexiWalkError) as e:
+                GpuGraph(dict(g, col=bad))
+            assert e.value.code == fw.FW_E_INVALID
+
+
+@pytest.mark.parametrize("where", [0, 77, -1])
+@pytest.mark.parametrize("bad", ["col_low", "col_high", "nan", "inf", "negative"])
+def test_bad_entries_are_refused(bad, where):
+    g = _rows([50, 1, 80], 300)
+    col, h = g["col"].copy(), g["h"].copy()
+    if bad.startswith("col"):
+        col[where] = -1 if bad == "col_low" else 300
+    else:
+        h[where] = {"nan": np.nan, "inf": np.inf, "negative": -1.0}[bad]
+    with pytest.raises(fw.FlexiWalkError) as e:
+        GpuGraph(dict(g, col=col, h=h))
+    assert e.value.code == fw.FW_E_INVALID
+
+
+@pytest.mark.parametrize("leaves,gap", [(1, 1), (64, 1), (129, 70), (3000, 7), (500, 5000)])
+def test_index_holds_every_entry(leaves, gap):
+    """Walks by the index equal walks that search the rows."""
+    g = _symmetric(leaves, gap)
+    starts = np.repeat(np.array([0, gap], np.int32), 700)
+    lg, pl = oracle.Logic(kind=oracle.NODE2VEC, weighted=True, p=4.0, q=0.25), oracle.Plan(rho=0.01)
+    out = []
+    for index in (False, True):
+        gg = GpuGraph(g, index=index)
+        try:
+            p, ln, _ = gpu_walk(gg, lg, pl, oracle.AUTO, starts, 20, 5)
+            out.append((np.asarray(p), np.asarray(ln)))
+        finally:
+            gg.close()
+    np.testing.assert_array_equal(out[0][0], out[1][0])
+    np.testing.assert_array_equal(out[0][1], out[1][1])
