@@ -570,7 +570,7 @@ int fw_graph_build_alias(fw_graph *g, void *stream)
     // out-of-range vertex
     hipError_t e = hipMemsetAsync(prop, 0, rec * ne, s);
     if (e == hipSuccess)
-        e = fw::launch_build_alias(g->row_ptr, g->col, g->h, g->label, g->nv, g->vrec, nullptr, (uint4 *)val.p,
+        e = fw::launch_build_alias(g->row_ptr, g->col, g->h, g->label, g->nv, g->ne, g->vrec, nullptr, (uint4 *)val.p,
                                    (int32_t *)idx.p, (ulonglong2 *)rowinfo.p, (int32_t *)hubs.p, (int *)nhub.p, prop,
                                    s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
@@ -641,7 +641,7 @@ int fw_graph_build_label_alias(fw_graph *g, void *stream)
     if (e == hipSuccess) e = hipMemcpyAsync(lrow + ng, &total, sizeof(int64_t), hipMemcpyHostToDevice, s);
     if (e == hipSuccess)
         e = fw::launch_build_alias(lrow, (const int32_t *)vcol.p, (const float *)vh.p, (const uint8_t *)vlab.p,
-                                   (int64_t)ng, g->vrec, (const float *)gmax.p, (uint4 *)val.p, (int32_t *)idx.p,
+                                   (int64_t)ng, g->ne, g->vrec, (const float *)gmax.p, (uint4 *)val.p, (int32_t *)idx.p,
                                    (ulonglong2 *)rowinfo.p, (int32_t *)hubs.p, (int *)nhub.p, lprop, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
     if (e != hipSuccess) {

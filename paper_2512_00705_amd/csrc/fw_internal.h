@@ -167,15 +167,13 @@ hipError_t launch_layout(const int64_t *row_ptr, const int32_t *col, const float
                          uint2 *edges, uint4 *vrec, uint32_t *start_hi, hipStream_t s);
 hipError_t launch_preprocess(const int64_t *row_ptr, const float *h, int64_t nv, uint4 *vrec, hipStream_t s);
 // Proposal records of h-proportional eRJS: Walker's alias table per row (the sweeping
-// construction in exact integer arithmetic, in parallel form: a scan pass and a merge
-// pass, one wave per row) written as prop[4k] = {col[k], h[k], col[a], h[a]},
-// prop[4k+1] = {threshold, lab[k] | lab[a] << 8, a, 0}, prop[4k+2..3] = vrec of col[k],
-// col[a].  Scratch: val (16 bytes) and idx (4 bytes) per entry, rowinfo (16 bytes) per row.
+// construction in exact integer arithmetic, in parallel form) written as
+// prop[4k] = {col[k], h[k], col[a], h[a]}, prop[4k+1] = {threshold, lab[k] | lab[a] << 8, a, 0},
+// prop[4k+2..3] = vrec of col[k], col[a].  Scratch: val (16 bytes) and idx (4 bytes) per entry,
+// rowinfo (16 bytes) and hubs (4 bytes) per row, nhub: one int.
 // rmax: each row's h maximum, or null to take it from vrec[row] (rows are vertices).
-// Rows longer than 8192 entries are merged one thread per entry (hubs: nv int32 of
-// scratch, nhub: one int).
 hipError_t launch_build_alias(const int64_t *row_ptr, const int32_t *col, const float *h, const uint8_t *label,
-                              int64_t nv, const uint4 *vrec, const float *rmax, uint4 *val, int32_t *idx,
+                              int64_t nv, int64_t ne, const uint4 *vrec, const float *rmax, uint4 *val, int32_t *idx,
                               ulonglong2 *rowinfo, int32_t *hubs, int *nhub, uint4 *prop, hipStream_t s);
 // Labels of a graph with label groups: at most this many (0 .. kMaxLabels - 1).
 constexpr int kMaxLabels = 16;

@@ -202,35 +202,22 @@ __global__ void __launch_bounds__(kBlock) validate_edges_kernel(const int64_t *r
 // result does not depend on the order of any sum.  A bucket keeping K units stores the
 // threshold min(floor(K * 2^32 / Q), 2^32 - 1).
 //
-// Pass 1 (one wave per row): Q, then each light entry's D and each heavy entry's E, the
-// light entries compacted at the row's front in index order and the heavy ones at its
-// back in reverse order (val: the 128-bit sum, idx: the entry's offset), and {Q, light
-// count} per row.  Pass 2 (one wave per row): both merges of the two sorted sequences,
-// 64 entries of each at a time, and the 64-byte record of every entry:
+// Pass 1 (a wave per row, a block for the longest): Q, then each light entry's D and each heavy
+// entry's E, the light entries' at the row's front in index order and the heavy ones' at its back
+// in reverse order (val: the sum at its place and each entry's place, idx: the entry of a place),
+// and {Q, light count} per row.  Pass 2 (a lane per entry): a search of the other sequence for
+// each entry's partner, and its 64-byte record:
 //   {col_k, bits(h_k), col_a, bits(h_a)}, {threshold, label_k | label_a << 8, a, 0},
 //   vrec[col_k], vrec[col_a]   (a: the alias's offset in the row).
+// Rows of up to 64 entries take both passes at once in registers.
 using u128 = unsigned __int128;
 
-// The sums of a row of n entries stay below n * Q <= n^2 * 2^32 (every q_k <= 2^32): 64 bits
-// hold them for rows of at most 2^15 entries, which take the 64-bit path (half the lane
-// exchanges of the 128-bit one).
-constexpr int64_t kAlias64Max = (int64_t)1 << 15;
-// Rows longer than this are merged by alias_hub_kernel, many waves per row.
+// Rows of at most this many entries are built whole by alias_small_kernel.
+constexpr int64_t kAliasSmallRow = kWave;
+// The sums of a row of n entries stay below n * Q <= n^2 * 2^32 (every q_k <= 2^32).  Longer rows
+// than this are scanned by alias_hub_scan_kernel, a block per row, with 128-bit sums; the others
+// by a wave with sums of 64 bits, which rows of up to 2^15 entries need.
 constexpr int64_t kAliasHubRow = 8192;
-// Rows of at most this many entries are built by alias_small_kernel, one lane per row.
-constexpr int64_t kAliasSmallRow = 16;
-
-template <typename T>
-__device__ __forceinline__ T shfl_t(T x, int src)
-{
-    if constexpr (sizeof(T) == 8) {
-        return (T)__shfl((long long)x, src, kWave);
-    } else {
-        const uint64_t lo = (uint64_t)__shfl((long long)(uint64_t)x, src, kWave);
-        const uint64_t hi = (uint64_t)__shfl((long long)(uint64_t)(x >> 64), src, kWave);
-        return ((u128)hi << 64) | lo;
-    }
-}
 
 template <typename T>
 __device__ __forceinline__ T shfl_up_t(T x, int d)
@@ -256,45 +243,73 @@ __device__ __forceinline__ T wave_incl_scan_t(T x)
     return x;
 }
 
-// A sum as stored in `val` (16 bytes, zero-extended from 64 bits).
-template <typename T>
-__device__ __forceinline__ T load_t(const uint4 *p)
-{
-    const uint4 x = *p;
-    if constexpr (sizeof(T) == 8) return ((uint64_t)x.y << 32) | (uint64_t)x.x;
-    else return ((u128)x.w << 96) | ((u128)x.z << 64) | ((u128)x.y << 32) | (u128)x.x;
-}
+// The scratch of a row that starts at entry b, 16 bytes per entry from val + b on: the sums at
+// their places (64 bits, or 94 in three words), and each entry's place.
+struct NarrowRow {
+    using Sum = uint64_t;
+    uint64_t *sums;
+    uint32_t *places;
+    __device__ NarrowRow(uint4 *val, int64_t b, int64_t n)
+        : sums(reinterpret_cast<uint64_t *>(val + b)), places(reinterpret_cast<uint32_t *>(sums + n)) {}
+    __device__ Sum sum(int64_t t) const { return sums[t]; }
+    __device__ void put(int64_t t, Sum x) const { sums[t] = x; }
+    __device__ uint32_t &place(int64_t k) const { return places[k]; }
+};
 
-template <typename T>
-__device__ __forceinline__ uint4 pack_t(T x)
-{
-    return make_uint4((uint32_t)x, (uint32_t)((uint64_t)x >> 32), (uint32_t)((u128)x >> 64), (uint32_t)((u128)x >> 96));
-}
+struct WideRow {
+    using Sum = u128;
+    uint4 *v;
+    __device__ WideRow(uint4 *val, int64_t b, int64_t) : v(val + b) {}
+    __device__ Sum sum(int64_t t) const
+    {
+        const uint32_t *w = &v[t].x;
+        return ((u128)w[2] << 64) | ((uint64_t)w[1] << 32) | w[0];
+    }
+    __device__ void put(int64_t t, Sum x) const
+    {
+        uint32_t *w = &v[t].x;
+        w[0] = (uint32_t)x;
+        w[1] = (uint32_t)((uint64_t)x >> 32);
+        w[2] = (uint32_t)(x >> 64);
+    }
+    __device__ uint32_t &place(int64_t k) const { return v[k].w; }
+};
 
 // q_k of the construction: h_k relative to the row maximum in 32 fractional bits.
+__device__ __forceinline__ uint64_t alias_q_of(float hk, float hmax)
+{
+    if (!(hmax > 0.0f)) return (uint64_t)1 << 32;
+    return (uint64_t)floor(((double)hk / (double)hmax) * 4294967296.0);
+}
+
 __device__ __forceinline__ uint64_t alias_q(const float *h, int64_t k, float hmax)
 {
-    if (h == nullptr || !(hmax > 0.0f)) return (uint64_t)1 << 32;
-    return (uint64_t)floor(((double)h[k] / (double)hmax) * 4294967296.0);
+    return h == nullptr ? (uint64_t)1 << 32 : alias_q_of(h[k], hmax);
 }
 
-__device__ __forceinline__ uint32_t alias_thr(u128 keep, uint64_t Q)
+// min(floor(keep * 2^32 / Q), 2^32 - 1), keep <= Q < 2^63.  The quotient in double is off by less
+// than 2^-18, so its integer part by at most one, which the exact products decide.
+__device__ __forceinline__ uint32_t alias_thr(uint64_t keep, uint64_t Q)
 {
-    const u128 t = (keep << 32) / (u128)Q;
-    return t >= (u128)0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)t;
+    if (keep >= Q) return 0xFFFFFFFFu;
+    uint64_t t = (uint64_t)((double)keep / (double)Q * 4294967296.0);
+    const u128 x = (u128)keep << 32, y = (u128)t * Q;
+    if (y > x) --t;
+    else if (x - y >= Q) ++t;
+    return t >= 0xFFFFFFFFu ? 0xFFFFFFFFu : (uint32_t)t;
 }
 
-// Pass 1 on row [b, b + n) with maximum hmax, sums of type T.
-template <typename T>
+// Pass 1 on row [b, b + n) with maximum hmax.
 __device__ __forceinline__ void alias_scan_row(const float *h, int64_t b, int64_t n, float hmax, uint4 *val,
                                                int32_t *idx, ulonglong2 *rowinfo_v)
 {
     const int lane = lane_id();
+    const NarrowRow row(val, b, n);
     const uint64_t below = lanes_below(lane);
     uint64_t qs = 0;
     for (int64_t k = lane; k < n; k += kWave) qs += alias_q(h, b + k, hmax);
     const uint64_t Q = wave_sum_u64(qs);
-    T dcarry = 0, ecarry = 0;
+    uint64_t dcarry = 0, ecarry = 0;
     int64_t nl = 0, nh = 0;
     for (int64_t k0 = 0; k0 < n; k0 += kWave) {
         const int64_t k = k0 + lane;
@@ -302,20 +317,22 @@ __device__ __forceinline__ void alias_scan_row(const float *h, int64_t b, int64_
         const uint64_t a = valid ? alias_q(h, b + k, hmax) * (uint64_t)n : 0;
         const bool light = valid && a < Q, heavy = valid && a >= Q;
         const uint64_t lm = __ballot(light), hm = __ballot(heavy);
-        const T d = light ? (T)(Q - a) : (T)0, e = heavy ? (T)(a - Q) : (T)0;
-        const T dinc = wave_incl_scan_t(d), einc = wave_incl_scan_t(e);
+        const uint64_t d = light ? Q - a : 0, e = heavy ? a - Q : 0;
+        const uint64_t dinc = wave_incl_scan_t(d), einc = wave_incl_scan_t(e);
         if (light) {
-            const int64_t pos = b + nl + __popcll(lm & below);
-            val[pos] = pack_t<T>(dcarry + dinc - d);  // deficits before this entry
-            idx[pos] = (int32_t)k;
+            const int64_t pos = nl + __popcll(lm & below);
+            row.put(pos, dcarry + dinc - d);  // deficits before this entry
+            idx[b + pos] = (int32_t)k;
+            row.place(k) = (uint32_t)pos;
         }
         if (heavy) {
-            const int64_t pos = b + n - 1 - (nh + __popcll(hm & below));
-            val[pos] = pack_t<T>(ecarry + einc);  // surplus up to and including this entry
-            idx[pos] = (int32_t)k;
+            const int64_t pos = n - 1 - (nh + __popcll(hm & below));
+            row.put(pos, ecarry + einc);  // surplus up to and including this entry
+            idx[b + pos] = (int32_t)k;
+            row.place(k) = (uint32_t)pos;
         }
-        dcarry += shfl_t(dinc, kWave - 1);
-        ecarry += shfl_t(einc, kWave - 1);
+        dcarry += (uint64_t)__shfl((long long)dinc, kWave - 1, kWave);
+        ecarry += (uint64_t)__shfl((long long)einc, kWave - 1, kWave);
         nl += __popcll(lm);
         nh += __popcll(hm);
     }
@@ -330,180 +347,157 @@ __global__ void __launch_bounds__(kBlock) alias_scan_kernel(const int64_t *row_p
     for (int64_t v = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; v < nv; v += nw) {
         const int64_t b = row_ptr[v];
         const int64_t n = row_ptr[v + 1] - b;
-        if (n <= kAliasSmallRow) continue;  // alias_small_kernel
+        if (n <= kAliasSmallRow || n > kAliasHubRow) continue;  // alias_small_kernel, alias_hub_scan_kernel
         const float hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
-        if (n <= kAlias64Max) alias_scan_row<uint64_t>(h, b, n, hmax, val, idx, rowinfo + v);
-        else alias_scan_row<u128>(h, b, n, hmax, val, idx, rowinfo + v);
+        alias_scan_row(h, b, n, hmax, val, idx, rowinfo + v);
     }
 }
 
-// Index of the first of the 64 wave lanes whose x (ascending over the lanes) is >= key
-// (ge) or > key (!ge); 64 when there is none.
-template <typename T>
-__device__ __forceinline__ int wave_bound_t(T x, T key, bool ge)
+// Each lane with `valid` gives record r0..r3 for prop[4 * at]; four lanes write one together, since
+// 16-byte pieces of 64 records per store are four times the requests (buf: 256 uint4 of LDS for
+// the wave; the parts are swizzled over its banks).  Every lane calls.
+__device__ __forceinline__ void write_records(uint4 *buf, bool valid, int64_t at, uint4 r0, uint4 r1, uint4 r2,
+                                              uint4 r3, uint4 *prop)
+{
+    const int lane = lane_id();
+    const uint64_t mask = __ballot(valid);
+    uint4 *const mine = buf + lane * 4;
+    const int sw = (lane >> 2) & 3;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the last records have been read
+    mine[0 ^ sw] = r0;
+    mine[1 ^ sw] = r1;
+    mine[2 ^ sw] = r2;
+    mine[3 ^ sw] = r3;
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int rec = i * 16 + lane / 4, part = lane & 3;
+        const int64_t k = (int64_t)__shfl((long long)at, rec, kWave);
+        if ((mask >> rec) & 1) prop[(int64_t)kPropU4 * k + part] = buf[rec * 4 + (part ^ ((rec >> 2) & 3))];
+    }
+}
+
+// Index of the first of the G lanes of the lane's group whose x (ascending over the lanes) is
+// >= key (ge) or > key (!ge); G when there is none.
+template <int G>
+__device__ __forceinline__ int group_bound(uint64_t x, uint64_t key, bool ge)
 {
     int c = 0;
 #pragma unroll
-    for (int s = kWave / 2; s > 0; s >>= 1) {
-        const T y = shfl_t(x, c + s - 1);
+    for (int s = G / 2; s > 0; s >>= 1) {
+        const uint64_t y = (uint64_t)__shfl((long long)x, c + s - 1, G);
         if (ge ? (y < key) : (y <= key)) c += s;
     }
-    // c in [0, 63]: one more test decides between c and 64
-    const T y = shfl_t(x, c);
+    const uint64_t y = (uint64_t)__shfl((long long)x, c, G);
     return (ge ? (y < key) : (y <= key)) ? c + 1 : c;
 }
 
-__device__ __forceinline__ void write_record(const int32_t *col, const float *h, const uint8_t *label,
-                                             const uint4 *vrec, int64_t b, int32_t k, int32_t al, uint32_t thr,
-                                             uint4 *prop)
+template <int G>
+__device__ __forceinline__ uint64_t group_scan(uint64_t x)
 {
-    const uint32_t hk = h ? __float_as_uint(h[b + k]) : __float_as_uint(1.0f);
-    const uint32_t ha = h ? __float_as_uint(h[b + al]) : __float_as_uint(1.0f);
-    const uint32_t lab = label ? ((uint32_t)label[b + k] | ((uint32_t)label[b + al] << 8)) : 0u;
-    const int32_t ck = col[b + k], ca = col[b + al];
-    uint4 *r = prop + (int64_t)kPropU4 * (b + k);
-    r[0] = make_uint4((uint32_t)ck, hk, (uint32_t)ca, ha);
-    r[1] = make_uint4(thr, lab, (uint32_t)al, 0u);
-    r[2] = vrec[ck];
-    r[3] = vrec[ca];
+    const int gl = lane_id() & (G - 1);
+#pragma unroll
+    for (int d = 1; d < G; d <<= 1) {
+        const uint64_t y = (uint64_t)__shfl_up((long long)x, d, G);
+        if (gl >= d) x += y;
+    }
+    return x;
 }
 
-// Pass 2 on row [b, b + n) with Q and nl from pass 1, sums of type T.
-template <typename T>
-__device__ __forceinline__ void alias_merge_row(const int32_t *col, const float *h, const uint8_t *label,
-                                                const uint4 *vrec, const uint4 *val, const int32_t *idx, int64_t b,
-                                                int64_t n, uint64_t Q, int64_t nl, float hmax, uint4 *prop)
+// Both passes for rows of at most G entries, a lane per entry, 64 / G rows at once: `rows` are the
+// lanes whose rows (b, n, hmax) are of this size.  The inclusive sums of the surplus and the
+// exclusive ones of the deficits ascend over the lanes, so the merges are searches of the group's
+// lanes.  A light entry with D > 0 finds the lane where the surplus reaches D, a heavy one; the
+// first (D = 0) takes the first heavy one.  Heavy entry j's D(n_j) is the first deficit sum above
+// E_j of any lane (lanes of heavy entries hold that of the next light one), or all of them.
+template <int G>
+__device__ __forceinline__ void alias_group_rows(uint64_t rows, const int32_t *col, const float *h,
+                                                 const uint8_t *label, const uint4 *vrec, int64_t b, int32_t n,
+                                                 float hmax, uint4 *buf, uint4 *prop)
 {
-    const int lane = lane_id();
-    constexpr T kMax = ~(T)0;
-    const int64_t nh = n - nl;  // >= 1 (the caller checked)
-    // heavy entry j (in index order) sits at b + n - 1 - j
-    const T e_last = load_t<T>(val + b + n - nh);
-    // light entries: alias = the first heavy entry whose E reaches the entry's D
-    for (int64_t li = 0, hj = 0; li < nl;) {
-        if (hj >= nh) {
-            // unreachable in exact arithmetic (the last E equals the total deficit, so
-            // every light entry finds its heavy one); kept so that the loop always ends
-            // and every record stays a valid self-alias
-            for (int64_t i = li + lane; i < nl; i += kWave) {
-                const int32_t k = idx[b + i];
-                write_record(col, h, label, vrec, b, k, k, 0xFFFFFFFFu, prop);
-            }
-            break;
+    const int lane = lane_id(), k = lane & (G - 1), gi = lane / G;
+    while (rows != 0) {
+        int src = -1;
+#pragma unroll
+        for (int i = 0; i < kWave / G; ++i) {
+            const int bit = rows != 0 ? __ffsll((unsigned long long)rows) - 1 : -1;
+            if (gi == i) src = bit;
+            rows &= rows - 1;  // (0 stays 0)
         }
-        const int64_t i = li + lane, j = hj + lane;
-        const T D = i < nl ? load_t<T>(val + b + i) : kMax;
-        const T E = j < nh ? load_t<T>(val + b + n - 1 - j) : kMax;
-        const int32_t hix = j < nh ? idx[b + n - 1 - j] : -1;
-        const int c = wave_bound_t(E, D, true);
-        const bool found = i < nl && c < kWave && hj + c < nh;
-        const int32_t al = __shfl(hix, c & (kWave - 1), kWave);
-        const int cnt = __popcll(__ballot(found));  // a prefix of the lanes (D ascends)
-        if (cnt == 0) {
-            hj += kWave;
-            continue;
+        const int64_t rb = (int64_t)__shfl((long long)b, src < 0 ? 0 : src, kWave);
+        const int32_t rn0 = __shfl(n, src < 0 ? 0 : src, kWave);
+        const float rh = __shfl(hmax, src < 0 ? 0 : src, kWave);
+        const int32_t rn = src < 0 ? 0 : rn0;
+        const bool valid = k < rn;
+        int32_t ck = 0;
+        float hk = 1.0f;
+        uint32_t lab = 0;
+        uint4 vr = make_uint4(0, 0, 0, 0);
+        uint64_t q = 0;
+        if (valid) {
+            ck = col[rb + k];
+            if (h) hk = h[rb + k];
+            if (label) lab = label[rb + k];
+            vr = vrec[ck];
+            q = h ? alias_q_of(hk, rh) : (uint64_t)1 << 32;
         }
-        if (found) {
-            const int32_t k = idx[b + i];
-            const uint64_t a = alias_q(h, b + k, hmax) * (uint64_t)n;
-            write_record(col, h, label, vrec, b, k, al, alias_thr((u128)a, Q), prop);
+        uint64_t Q = q;
+#pragma unroll
+        for (int d = G / 2; d > 0; d >>= 1) Q += (uint64_t)__shfl_xor((long long)Q, d, G);
+        const uint64_t a = q * (uint64_t)rn;
+        const bool heavy = valid && a >= Q;
+        const uint64_t dinc = group_scan<G>(valid && !heavy ? Q - a : 0);
+        const uint64_t E = group_scan<G>(heavy ? a - Q : 0);
+        const uint64_t D = dinc - (valid && !heavy ? Q - a : 0);
+        const uint64_t total = (uint64_t)__shfl((long long)E, G - 1, G);
+        uint64_t hm = __ballot(heavy) >> (gi * G);
+        if (G < kWave) hm &= ((uint64_t)1 << (G & 63)) - 1;
+        const int ce = group_bound<G>(E, D, true), cd = group_bound<G>(D, E, false);
+        const uint64_t dn = (uint64_t)__shfl((long long)D, cd & (G - 1), G);
+        uint64_t keep = a;
+        int al = D == 0 ? __ffsll((unsigned long long)hm) - 1 : ce;
+        if (heavy) {
+            keep = Q + E - (cd < G ? dn : total);
+            const uint64_t later = (hm >> k) & ~(uint64_t)1;
+            al = keep < Q && later != 0 ? k + __ffsll((unsigned long long)later) - 1 : k;
+        } else if (al < 0 || al >= rn) {  // unreachable in exact arithmetic; a valid self-alias
+            al = k;
+            keep = Q;
         }
-        li += cnt;
-    }
-    // heavy entries: keep Q + E_j - D(n_j), alias the next heavy entry unless full
-    for (int64_t hj = 0, li = 0; hj < nh;) {
-        const int64_t i = li + lane, j = hj + lane;
-        const T D = i < nl ? load_t<T>(val + b + i) : kMax;
-        const T E = j < nh ? load_t<T>(val + b + n - 1 - j) : kMax;
-        const int c = wave_bound_t(D, E, false);  // light entries with D <= E_j in this block
-        const bool found = j < nh && c < kWave;
-        const T dn = shfl_t(D, c & (kWave - 1));
-        const int cnt = __popcll(__ballot(found));  // a prefix of the lanes (E ascends)
-        if (cnt == 0) {
-            li += kWave;
-            continue;
-        }
-        if (found) {
-            const T spent = li + c < nl ? dn : e_last;
-            const T keep = (T)Q + E - spent;
-            const int32_t k = idx[b + n - 1 - j];
-            const int32_t al = (keep < (T)Q && j + 1 < nh) ? idx[b + n - 2 - j] : k;
-            write_record(col, h, label, vrec, b, k, al, alias_thr((u128)keep, Q), prop);
-        }
-        hj += cnt;
-    }
-}
-
-__global__ void __launch_bounds__(kBlock) alias_merge_kernel(const int64_t *row_ptr, const int32_t *col,
-                                                             const float *h, const uint8_t *label, int64_t nv,
-                                                             const uint4 *vrec, const float *rmax, const uint4 *val,
-                                                             const int32_t *idx, const ulonglong2 *rowinfo,
-                                                             uint4 *prop)
-{
-    const int lane = lane_id();
-    const int64_t nw = (int64_t)gridDim.x * (kBlock / kWave);
-    for (int64_t v = (int64_t)blockIdx.x * (kBlock / kWave) + threadIdx.x / kWave; v < nv; v += nw) {
-        const int64_t b = row_ptr[v];
-        const int64_t n = row_ptr[v + 1] - b;
-        if (n <= kAliasSmallRow) continue;  // alias_small_kernel
-        const ulonglong2 ri = rowinfo[v];
-        const uint64_t Q = (uint64_t)ri.x;
-        const int64_t nl = (int64_t)ri.y;
-        if (n - nl <= 0) {  // unreachable (the a_k sum to n * Q); every record stays a valid self-alias
-            for (int64_t k = lane; k < n; k += kWave)
-                write_record(col, h, label, vrec, b, (int32_t)k, (int32_t)k, 0xFFFFFFFFu, prop);
-            continue;
-        }
-        if (n > kAliasHubRow) continue;  // alias_hub_kernel
-        const float hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
-        if (n <= kAlias64Max) alias_merge_row<uint64_t>(col, h, label, vrec, val, idx, b, n, Q, nl, hmax, prop);
-        else alias_merge_row<u128>(col, h, label, vrec, val, idx, b, n, Q, nl, hmax, prop);
+        al &= G - 1;
+        const int32_t ca = __shfl(ck, al, G);
+        const float ha = __shfl(hk, al, G);
+        const uint32_t la = __shfl(lab, al, G);
+        const uint4 va = make_uint4(__shfl(vr.x, al, G), __shfl(vr.y, al, G), __shfl(vr.z, al, G), __shfl(vr.w, al, G));
+        write_records(buf, valid, rb + k, make_uint4((uint32_t)ck, __float_as_uint(hk), (uint32_t)ca, __float_as_uint(ha)),
+                      make_uint4(valid ? alias_thr(keep, Q) : 0u, lab | (la << 8), (uint32_t)al, 0u), vr, va, prop);
     }
 }
 
-// Rows of 1 .. kAliasSmallRow entries, one lane per row: the sweep itself, in entry order.
-// A(k) = q_k * n.  With the current heavy entry j holding residual r: each light entry i
-// (A < Q) first closes the heavy entries whose residual has fallen below Q (bucket j keeps
-// r, aliased to the next heavy entry, which then holds A(j') - (Q - r)), then keeps A(i)
-// with j as its alias, and r loses Q - A(i); the heavy entries left at the end are closed
-// the same way, a full bucket being its own alias.  This is the table the two passes
-// above build for longer rows (sums here stay below 16 * 16 * 2^32).
+// Rows of 1 .. kAliasSmallRow entries: each wave takes 64 consecutive rows, by length in groups of
+// 8, 16, 32 or 64 lanes per row.  Nothing goes through memory between the two passes, and the
+// alias's part of a record comes from its lane (scale 20, the rows of up to 16 entries alone
+// took 1.27 ms with a lane per row sweeping its entries one after another).
 __global__ void __launch_bounds__(256) alias_small_kernel(const int64_t *row_ptr, const int32_t *col, const float *h,
                                                           const uint8_t *label, int64_t nv, const uint4 *vrec,
                                                           const float *rmax, uint4 *prop)
 {
-    for (int64_t v = (int64_t)blockIdx.x * 256 + threadIdx.x; v < nv; v += (int64_t)gridDim.x * 256) {
-        const int64_t b = row_ptr[v];
-        const int32_t n = (int32_t)(row_ptr[v + 1] - b);
-        if (n == 0 || n > kAliasSmallRow) continue;
-        const float hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
-        uint64_t Q = 0;
-        for (int32_t k = 0; k < n; ++k) Q += alias_q(h, b + k, hmax);
-        auto A = [&](int32_t k) { return alias_q(h, b + k, hmax) * (uint64_t)n; };
-        int32_t j = 0;
-        while (A(j) < Q) ++j;  // the first heavy entry (the A sum to n * Q)
-        uint64_t r = A(j);
-        for (int32_t i = 0; i < n; ++i) {
-            const uint64_t ai = A(i);
-            if (ai >= Q) continue;
-            while (r < Q) {  // a later heavy entry exists while a light entry is left
-                int32_t jn = j + 1;
-                while (jn < n - 1 && A(jn) < Q) ++jn;
-                write_record(col, h, label, vrec, b, j, jn, alias_thr((u128)r, Q), prop);
-                r = A(jn) - (Q - r);
-                j = jn;
-            }
-            write_record(col, h, label, vrec, b, i, j, alias_thr((u128)ai, Q), prop);
-            r -= Q - ai;
+    __shared__ uint4 bufs[4][kWave * 4];
+    uint4 *const buf = bufs[threadIdx.x / kWave];
+    const int64_t nw = (int64_t)gridDim.x * 4;
+    for (int64_t v0 = ((int64_t)blockIdx.x * 4 + threadIdx.x / kWave) * kWave; v0 < nv; v0 += nw * kWave) {
+        const int64_t v = v0 + lane_id();
+        int64_t b = 0, n = 0;
+        float hmax = 0.0f;
+        if (v < nv) {
+            b = row_ptr[v];
+            n = row_ptr[v + 1] - b;
+            hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
         }
-        for (;;) {
-            int32_t jn = j + 1;
-            while (jn < n && A(jn) < Q) ++jn;
-            write_record(col, h, label, vrec, b, j, (r < Q && jn < n) ? jn : j, alias_thr((u128)r, Q), prop);
-            if (jn >= n) break;
-            r = A(jn) - (Q - r);
-            j = jn;
-        }
+        alias_group_rows<8>(__ballot(n > 0 && n <= 8), col, h, label, vrec, b, (int32_t)n, hmax, buf, prop);
+        alias_group_rows<16>(__ballot(n > 8 && n <= 16), col, h, label, vrec, b, (int32_t)n, hmax, buf, prop);
+        alias_group_rows<32>(__ballot(n > 16 && n <= 32), col, h, label, vrec, b, (int32_t)n, hmax, buf, prop);
+        alias_group_rows<64>(__ballot(n > 32 && n <= kAliasSmallRow), col, h, label, vrec, b, (int32_t)n, hmax, buf, prop);
     }
 }
 
@@ -515,63 +509,166 @@ __global__ void __launch_bounds__(256) alias_hub_list_kernel(const int64_t *row_
         if (row_ptr[v + 1] - row_ptr[v] > kAliasHubRow) hubs[atomicAdd(nhub, 1)] = (int32_t)v;
 }
 
-// Pass 2 for the long rows, one thread per entry (blockIdx.y picks the row, the blocks of a
-// row stride over its entries): the same two merges, each entry finding its partner by a
-// binary search of the other sorted sequence instead of a wave walking the row, so that a
-// hub row is spread over many waves.  Light entry i: alias = the first heavy entry with
-// E >= D_i.  Heavy entry j: keep Q + E_j - D(first light entry with D > E_j, or the last
-// E), alias the next heavy entry unless it keeps a full bucket.
-__global__ void __launch_bounds__(256) alias_hub_kernel(const int64_t *row_ptr, const int32_t *col, const float *h,
-                                                        const uint8_t *label, const uint4 *vrec, const float *rmax,
-                                                        const uint4 *val, const int32_t *idx,
-                                                        const ulonglong2 *rowinfo, const int32_t *hubs,
-                                                        const int *nhub, uint4 *prop)
+// Pass 1 for the longest rows, a block of 1024 threads per row, two entries per thread at a time
+// (scale 20, rows of up to 10^5: 1.77 ms with a wave per row, 0.28 so).
+__global__ void __launch_bounds__(1024) alias_hub_scan_kernel(const int64_t *row_ptr, const float *h, const uint4 *vrec,
+                                                              const float *rmax, uint4 *val, int32_t *idx,
+                                                              ulonglong2 *rowinfo, const int32_t *hubs, const int *nhub)
 {
-    const int nh_rows = *nhub;
-    for (int hr = blockIdx.y; hr < nh_rows; hr += gridDim.y) {
+    constexpr int kPer = 2, kWaves = 1024 / kWave;
+    __shared__ uint64_t wq[kWaves];
+    __shared__ u128 wd[kWaves], we[kWaves];
+    __shared__ int wl[kWaves];
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const int rows = *nhub;
+    for (int hr = blockIdx.x; hr < rows; hr += gridDim.x) {
         const int64_t v = hubs[hr];
         const int64_t b = row_ptr[v];
         const int64_t n = row_ptr[v + 1] - b;
-        const ulonglong2 ri = rowinfo[v];
-        const uint64_t Q = (uint64_t)ri.x;
-        const int64_t nl = (int64_t)ri.y, nh = n - nl;
+        if (n <= kAliasHubRow) continue;  // (the same for the whole block)
+        const WideRow row(val, b, n);
         const float hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
-        for (int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x; t < n; t += (int64_t)gridDim.x * 256) {
-            if (nh <= 0) {  // unreachable (the a_k sum to n * Q); a valid self-alias
-                write_record(col, h, label, vrec, b, (int32_t)t, (int32_t)t, 0xFFFFFFFFu, prop);
-                continue;
+        uint64_t qs = 0;
+        for (int64_t k = threadIdx.x; k < n; k += 1024) qs += alias_q(h, b + k, hmax);
+        qs = wave_sum_u64(qs);
+        if (lane == 0) wq[wave] = qs;
+        __syncthreads();
+        uint64_t Q = 0;
+        for (int w = 0; w < kWaves; ++w) Q += wq[w];
+        u128 dcarry = 0, ecarry = 0;
+        int64_t nl = 0;
+        for (int64_t k0 = 0; k0 < n; k0 += 1024 * kPer) {
+            const int64_t kt = k0 + (int64_t)threadIdx.x * kPer;
+            uint64_t a[kPer];
+            u128 td = 0, te = 0;
+            int tl = 0;
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                a[i] = kt + i < n ? alias_q(h, b + kt + i, hmax) * (uint64_t)n : Q;  // (past the end: no deficit, no surplus)
+                td += a[i] < Q ? Q - a[i] : 0;
+                te += a[i] < Q ? 0 : a[i] - Q;
+                tl += a[i] < Q ? 1 : 0;
             }
-            if (t < nl) {
-                const u128 D = load_t<u128>(val + b + t);
-                int64_t lo = 0, hi = nh;  // first heavy j with E_j >= D (E_j at b + n - 1 - j, ascending in j)
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (load_t<u128>(val + b + n - 1 - mid) < D) lo = mid + 1;
-                    else hi = mid;
+            const u128 dinc = wave_incl_scan_t(td), einc = wave_incl_scan_t(te);
+            int linc = tl;
+#pragma unroll
+            for (int d = 1; d < kWave; d <<= 1) {
+                const int y = __shfl_up(linc, d, kWave);
+                if (lane >= d) linc += y;
+            }
+            __syncthreads();  // the last tile's (or row's) sums have been read
+            if (lane == kWave - 1) {
+                wd[wave] = dinc;
+                we[wave] = einc;
+                wl[wave] = linc;
+            }
+            __syncthreads();
+            u128 d = dcarry + dinc - td, e = ecarry + einc - te;
+            int64_t l = nl + linc - tl;
+#pragma unroll 1
+            for (int w = 0; w < kWaves; ++w) {
+                if (w < wave) {
+                    d += wd[w];
+                    e += we[w];
+                    l += wl[w];
                 }
-                const int32_t k = idx[b + t];
-                if (lo >= nh) {  // unreachable in exact arithmetic; a valid self-alias
-                    write_record(col, h, label, vrec, b, k, k, 0xFFFFFFFFu, prop);
-                    continue;
+                dcarry += wd[w];
+                ecarry += we[w];
+                nl += wl[w];
+            }
+#pragma unroll
+            for (int i = 0; i < kPer; ++i) {
+                if (kt + i >= n) break;
+                int64_t pos;
+                if (a[i] < Q) {
+                    pos = l;
+                    row.put(pos, d);  // deficits before this entry
+                    d += Q - a[i];
+                    ++l;
+                } else {
+                    pos = n - 1 - (kt + i - l);
+                    e += a[i] - Q;
+                    row.put(pos, e);  // surplus up to and including this entry
                 }
-                const uint64_t a = alias_q(h, b + k, hmax) * (uint64_t)n;
-                write_record(col, h, label, vrec, b, k, idx[b + n - 1 - lo], alias_thr((u128)a, Q), prop);
-            } else {
-                const int64_t j = t - nl;
-                const u128 E = load_t<u128>(val + b + n - 1 - j);
-                int64_t lo = 0, hi = nl;  // first light i with D_i > E (D ascending in i)
-                while (lo < hi) {
-                    const int64_t mid = (lo + hi) >> 1;
-                    if (load_t<u128>(val + b + mid) <= E) lo = mid + 1;
-                    else hi = mid;
-                }
-                const u128 spent = lo < nl ? load_t<u128>(val + b + lo) : load_t<u128>(val + b + n - nh);
-                const u128 keep = (u128)Q + E - spent;
-                const int32_t k = idx[b + n - 1 - j];
-                const int32_t al = (keep < (u128)Q && j + 1 < nh) ? idx[b + n - 2 - j] : k;
-                write_record(col, h, label, vrec, b, k, al, alias_thr(keep, Q), prop);
+                idx[b + pos] = (int32_t)(kt + i);
+                row.place(kt + i) = (uint32_t)pos;
             }
         }
+        if (threadIdx.x == 0) rowinfo[v] = make_ulonglong2((unsigned long long)Q, (unsigned long long)nl);
+    }
+}
+
+// The alias of the entry at place t (-1: itself), and what a heavy one keeps.
+template <typename Row>
+__device__ __forceinline__ void alias_partner(const Row row, const int32_t *idx, int64_t b, int64_t n, int64_t nl,
+                                              uint64_t Q, int64_t t, int32_t &al, uint64_t &keep)
+{
+    using T = typename Row::Sum;
+    // A light entry looks for the first heavy j with E_j >= D (E_j at n - 1 - j), a heavy one for
+    // the first light i with D_i > E (at i); sums ascend in i and j.  One loop for both, since a
+    // wave has lanes of both: sum < key, key = D or E + 1.
+    const bool light = t < nl;
+    const T mine = row.sum(t), key = light ? mine : mine + 1;
+    const int64_t at0 = light ? n - 1 : 0, dir = light ? -1 : 1;
+    const int64_t m = light ? n - nl : nl;
+    int64_t lo = 0, hi = m;
+    while (lo < hi) {
+        const int64_t mid = (lo + hi) >> 1;
+        if (row.sum(at0 + dir * mid) < key) lo = mid + 1;
+        else hi = mid;
+    }
+    if (light) {
+        al = lo < m ? idx[b + n - 1 - lo] : -1;  // (always there in exact arithmetic)
+    } else {
+        const T spent = row.sum(lo);  // (lo == nl: the last E, all the deficits)
+        keep = (uint64_t)((T)Q + mine - spent);
+        al = (keep < Q && t > nl) ? idx[b + t - 1] : -1;
+    }
+}
+
+// Pass 2 for the rows longer than kAliasSmallRow, a lane per entry in the graph's order, so that
+// reads and records are consecutive; each finds its partner by a binary search of the other
+// sorted sequence, where neighbouring lanes search alike (scale 20: 1.60 ms; a wave per row
+// merging 64 entries of both sequences at a time, entries and records in the order of the sums,
+// 2.05 ms).
+__global__ void __launch_bounds__(kBlock) alias_record_kernel(const int64_t *row_ptr, const int32_t *col,
+                                                              const float *h, const uint8_t *label, int64_t nv,
+                                                              int64_t ne, const uint4 *vrec, const float *rmax,
+                                                              uint4 *val, const int32_t *idx,
+                                                              const ulonglong2 *rowinfo, uint4 *prop)
+{
+    __shared__ uint4 bufs[kWavesPerBlock][kWave * 4];
+    uint4 *const buf = bufs[threadIdx.x / kWave];
+    const EntrySpan sp = entry_span(ne);
+    int64_t r0 = -1;
+    for (int64_t k0 = sp.k; k0 < sp.end; k0 += kWave) {
+        const int64_t v = rows_of_entries(row_ptr, nv, k0, sp.end, r0);
+        const int64_t e = k0 + lane_id(), b = row_ptr[v], n = row_ptr[v + 1] - b, k = e - b;
+        const bool valid = e < sp.end && n > kAliasSmallRow;
+        if (__ballot(valid) == 0) continue;
+        uint4 r0v = make_uint4(0, 0, 0, 0), r1v = r0v, r2v = r0v, r3v = r0v;
+        if (valid) {
+            const ulonglong2 ri = rowinfo[v];
+            const uint64_t Q = (uint64_t)ri.x;
+            const int64_t nl = (int64_t)ri.y;
+            const float hmax = rmax ? rmax[v] : __uint_as_float(vrec[v].z);
+            const bool wide = n > kAliasHubRow;
+            const int64_t t = wide ? WideRow(val, b, n).place(k) : NarrowRow(val, b, n).place(k);
+            int32_t al;
+            uint64_t keep = t < nl ? alias_q(h, e, hmax) * (uint64_t)n : Q;
+            if (wide) alias_partner(WideRow(val, b, n), idx, b, n, nl, Q, t, al, keep);
+            else alias_partner(NarrowRow(val, b, n), idx, b, n, nl, Q, t, al, keep);
+            if (al < 0 && t < nl) keep = Q;  // unreachable in exact arithmetic; a valid self-alias
+            const int64_t ea = al < 0 ? e : b + al;
+            const int32_t ck = col[e], ca = col[ea];
+            r0v = make_uint4((uint32_t)ck, __float_as_uint(h ? h[e] : 1.0f), (uint32_t)ca,
+                             __float_as_uint(h ? h[ea] : 1.0f));
+            r1v = make_uint4(alias_thr(keep, Q), label ? ((uint32_t)label[e] | ((uint32_t)label[ea] << 8)) : 0u,
+                             (uint32_t)(ea - b), 0u);
+            r2v = vrec[ck];
+            r3v = vrec[ca];
+        }
+        write_records(buf, valid, e, r0v, r1v, r2v, r3v, prop);
     }
 }
 
@@ -811,35 +908,32 @@ hipError_t launch_export_alias(const uint4 *prop, int64_t ne, uint32_t *thr, int
 }
 
 hipError_t launch_build_alias(const int64_t *row_ptr, const int32_t *col, const float *h, const uint8_t *label,
-                              int64_t nv, const uint4 *vrec, const float *rmax, uint4 *val, int32_t *idx,
+                              int64_t nv, int64_t ne, const uint4 *vrec, const float *rmax, uint4 *val, int32_t *idx,
                               ulonglong2 *rowinfo, int32_t *hubs, int *nhub, uint4 *prop, hipStream_t s)
 {
     int64_t blocks = (nv + kWavesPerBlock - 1) / kWavesPerBlock;
     if (blocks > 65536) blocks = 65536;
     if (blocks < 1) blocks = 1;
+    // the long rows, listed
+    const unsigned lb = (unsigned)std::max<int64_t>(1, std::min<int64_t>(4096, (nv + 255) / 256));
+    hipError_t e = hipMemsetAsync(nhub, 0, sizeof(int), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(alias_hub_list_kernel, dim3(lb), dim3(256), 0, s, row_ptr, nv, hubs, nhub);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    // sums: a block per row for the longest, a wave for the others
+    hipLaunchKernelGGL(alias_hub_scan_kernel, dim3(512), dim3(1024), 0, s, row_ptr, h, vrec, rmax, val, idx, rowinfo,
+                       hubs, nhub);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
     hipLaunchKernelGGL(alias_scan_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, row_ptr, h, nv, vrec, rmax, val,
                        idx, rowinfo);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(alias_merge_kernel, dim3((unsigned)blocks), dim3(kBlock), 0, s, row_ptr, col, h, label, nv,
-                       vrec, rmax, val, idx, rowinfo, prop);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the short rows, one lane each
-    int64_t sb = (nv + 255) / 256;
-    if (sb > 65536) sb = 65536;
-    if (sb < 1) sb = 1;
+    // records: a lane per entry, the short rows 64 per wave
+    hipLaunchKernelGGL(alias_record_kernel, dim3(entry_blocks(ne)), dim3(kBlock), 0, s, row_ptr, col, h, label,
+                       nv, ne, vrec, rmax, val, idx, rowinfo, prop);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    const int64_t sb = std::max<int64_t>(1, std::min<int64_t>(65536, (nv + 255) / 256));
     hipLaunchKernelGGL(alias_small_kernel, dim3((unsigned)sb), dim3(256), 0, s, row_ptr, col, h, label, nv, vrec, rmax,
                        prop);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    // the long rows: listed, then one thread per entry
-    if ((e = hipMemsetAsync(nhub, 0, sizeof(int), s)) != hipSuccess) return e;
-    int64_t lb = (nv + 255) / 256;
-    if (lb > 4096) lb = 4096;
-    if (lb < 1) lb = 1;
-    hipLaunchKernelGGL(alias_hub_list_kernel, dim3((unsigned)lb), dim3(256), 0, s, row_ptr, nv, hubs, nhub);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(alias_hub_kernel, dim3(64, 1024), dim3(256), 0, s, row_ptr, col, h, label, vrec, rmax, val, idx,
-                       rowinfo, hubs, nhub, prop);
     return hipGetLastError();
 }
 

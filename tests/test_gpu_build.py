@@ -121,3 +121,28 @@ def test_index_holds_every_entry(leaves, gap):
             gg.close()
     np.testing.assert_array_equal(out[0][0], out[1][0])
     np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
+@pytest.mark.parametrize("weights", ["random", "equal", "zeros", "one_heavy", "none"])
+@pytest.mark.parametrize("lens", [[1, 7, 8, 9, 15, 16, 17, 31, 32, 33, 63, 64], [65, 1, 127, 128, 129, 64, 1000],
+                                  [8191, 8192, 8193, 2, 66], [10241, 3, 32768, 32769, 70]])
+def test_alias_tables_of_row_lengths(lens, weights):
+    """Rows built whole by a few lanes, by a wave's sums, by a block's: equal to the sequential sweep."""
+    g = _rows(lens, 40000)
+    if weights == "equal":
+        g["h"][:] = 3.0
+    elif weights == "zeros":
+        g["h"][np.arange(g["ne"]) % 3 != 1] = 0.0
+        g["h"][g["row_ptr"][1] : g["row_ptr"][2]] = 0.0
+    elif weights == "one_heavy":
+        g["h"][g["row_ptr"][1 : len(lens) + 1] - 1] = 1e6
+    elif weights == "none":
+        g["h"] = None
+    gg = GpuGraph(g, alias=True)
+    try:
+        thr, al = fw.fw_graph_export_alias(gg.handle, gg.ne)
+    finally:
+        gg.close()
+    othr, oal = oracle.Graph(g).alias()
+    np.testing.assert_array_equal(al, oal)
+    np.testing.assert_array_equal(thr, othr)
