@@ -16,6 +16,7 @@
 #include "fw_device.h"
 #include "fw_internal.h"
 #include "fw_host.h"
+#include "fw_pool.h"
 
 namespace fw {
 namespace host {
@@ -55,20 +56,25 @@ using fw::host::plan_args;
 static void graph_free(fw_graph *g)
 {
     if (!g) return;
-    (void)hipFree(g->row_ptr);
-    (void)hipFree(g->col);
-    (void)hipFree(g->h);
-    (void)hipFree(g->label);
-    (void)hipFree(g->edges);
-    (void)hipFree(g->erec8);
-    (void)hipFree(g->vrec);
-    (void)hipFree(g->start_hi);
-    (void)hipFree(g->scratch);
-    (void)hipFree(g->mtab);
-    (void)hipFree(g->prop);
-    (void)hipFree(g->lrow);
-    (void)hipFree(g->lprop);
+    // hipFree waits for all the device's work (also that of a small block): after it nothing uses
+    // the graph's memory any more.  During another stream's capture it can fail; the other
+    // blocks then go the same way.
+    const bool unused = g->scratch && hipFree(g->scratch) == hipSuccess;
+    for (void *p : {(void *)g->row_ptr, (void *)g->col, (void *)g->h, (void *)g->label, (void *)g->edges,
+                    (void *)g->erec8, (void *)g->vrec, (void *)g->start_hi, (void *)g->mtab, (void *)g->prop,
+                    (void *)g->lrow, (void *)g->lprop})
+        fw::dev_pool().free(p, unused);
+    fw::dev_pool().turn();
     delete g;
+}
+
+template <typename P>
+static hipError_t pool_malloc(P **p, size_t bytes)
+{
+    void *v = nullptr;
+    const hipError_t e = fw::dev_pool().alloc(&v, bytes);
+    *p = (P *)v;
+    return e;
 }
 
 template <typename T>
@@ -76,8 +82,7 @@ static int dev_copy(T **dst, const T *src, int64_t count, int on_device)
 {
     // whole 16-byte parts: the walk reads single entries of col in aligned parts of 16 bytes
     const size_t bytes = (sizeof(T) * (size_t)(count > 0 ? count : 1) + 15) / 16 * 16;
-    if (hipMalloc((void **)dst, bytes) != hipSuccess) {
-        *dst = nullptr;
+    if (pool_malloc(dst, bytes) != hipSuccess) {
         return fail(FW_E_NOMEM, "hipMalloc of %zu bytes failed", bytes);
     }
     if (count > 0) HIP_TRY(hipMemcpy(*dst, src, sizeof(T) * (size_t)count,
@@ -85,10 +90,11 @@ static int dev_copy(T **dst, const T *src, int64_t count, int on_device)
     return FW_OK;
 }
 
-// device memory freed at scope exit
+// device memory freed at scope exit; unused: the work that uses it has been waited for
 struct DevBuf {
     void *p = nullptr;
-    ~DevBuf() { (void)hipFree(p); }
+    bool unused = false;
+    ~DevBuf() { fw::dev_pool().free(p, unused); }
 };
 
 extern "C" {
@@ -129,7 +135,7 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
             graph_free(g);
             return rc;
         }
-        if (hipMalloc((void **)&g->h, sizeof(float) * (size_t)(g->ne > 0 ? g->ne : 1)) != hipSuccess) {
+        if (pool_malloc(&g->h, sizeof(float) * (size_t)(g->ne > 0 ? g->ne : 1)) != hipSuccess) {
             graph_free(g);
             return fail(FW_E_NOMEM, "fw_graph_create: hipMalloc failed");
         }
@@ -143,11 +149,11 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     const bool wide = g->ne >= ((int64_t)1 << 32);
     // (edge records in whole 16-byte parts, as the walk reads them)
     const size_t parts4 = ((size_t)g->ne + 3) / 4 + 1, parts2 = ((size_t)g->ne + 1) / 2 + 1;
-    if ((packed && hipMalloc((void **)&g->erec8, 16 * parts4) != hipSuccess) ||
-        (!packed && hipMalloc((void **)&g->edges, 16 * parts2) != hipSuccess) ||
-        hipMalloc((void **)&g->vrec, sizeof(uint4) * (size_t)(g->nv > 0 ? g->nv : 1)) != hipSuccess ||
-        (wide && hipMalloc((void **)&g->start_hi, sizeof(uint32_t) * (size_t)g->nv) != hipSuccess) ||
-        hipMalloc((void **)&g->scratch, (4 + fw::kQueueWords) * sizeof(unsigned long long)) != hipSuccess) {
+    if ((packed && pool_malloc(&g->erec8, 16 * parts4) != hipSuccess) ||
+        (!packed && pool_malloc(&g->edges, 16 * parts2) != hipSuccess) ||
+        pool_malloc(&g->vrec, sizeof(uint4) * (size_t)(g->nv > 0 ? g->nv : 1)) != hipSuccess ||
+        (wide && pool_malloc(&g->start_hi, sizeof(uint32_t) * (size_t)g->nv) != hipSuccess) ||
+        fw::dev_malloc(&g->scratch, (4 + fw::kQueueWords) * sizeof(unsigned long long)) != hipSuccess) {
         graph_free(g);
         return fail(FW_E_NOMEM, "fw_graph_create: hipMalloc failed");
     }
@@ -196,6 +202,7 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     if (e == hipSuccess && packed) e = fw::launch_pack8(g->col, (const uint8_t *)codes.p, g->ne, g->erec8, nullptr);
     if (e == hipSuccess) e = hipMemset(g->scratch, 0, (4 + fw::kQueueWords) * sizeof(unsigned long long));
     if (e == hipSuccess) e = hipDeviceSynchronize();
+    codes.unused = e == hipSuccess;
     if (e != hipSuccess) {
         graph_free(g);
         return fail(FW_E_DEVICE, "fw_graph_create: %s", hipGetErrorString(e));
@@ -229,14 +236,14 @@ int fw_graph_build_index(fw_graph *g, void *stream)
     uint64_t buckets = 1;
     while (buckets * fw::kIndexSlots < 2 * (uint64_t)g->ne) buckets <<= 1;
     unsigned long long *tab = nullptr;
-    if (hipMalloc((void **)&tab, buckets * bucket_bytes) != hipSuccess)
+    if (pool_malloc(&tab, buckets * bucket_bytes) != hipSuccess)
         return fail(FW_E_NOMEM, "fw_graph_build_index: hipMalloc of %llu bytes failed",
                     (unsigned long long)(buckets * bucket_bytes));
     hipStream_t s = (hipStream_t)stream;
     hipError_t e = hipMemsetAsync(tab, 0xFF, buckets * bucket_bytes, s);  // every key kEmptyKey
     if (e == hipSuccess) e = fw::launch_build_index(g->row_ptr, g->col, g->h, g->nv, g->ne, tab, buckets - 1, s);
     if (e != hipSuccess) {
-        (void)hipFree(tab);
+        fw::dev_pool().free(tab, false);
         return fail(FW_E_DEVICE, "fw_graph_build_index: %s", hipGetErrorString(e));
     }
     g->mtab = tab;
@@ -269,8 +276,8 @@ int fw_graph_export_alias(const fw_graph *g, uint32_t *thr, int32_t *alias)
     HIP_TRY(hipDeviceSynchronize());
     // gathered on the device from the second uint4 of each record, then copied whole
     DevBuf dt, da;
-    HIP_TRY(hipMalloc(&dt.p, sizeof(uint32_t) * (size_t)g->ne));
-    HIP_TRY(hipMalloc(&da.p, sizeof(int32_t) * (size_t)g->ne));
+    HIP_TRY(fw::dev_malloc(&dt.p, sizeof(uint32_t) * (size_t)g->ne));
+    HIP_TRY(fw::dev_malloc(&da.p, sizeof(int32_t) * (size_t)g->ne));
     HIP_TRY(fw::launch_export_alias(g->prop, g->ne, (uint32_t *)dt.p, (int32_t *)da.p, nullptr));
     HIP_TRY(hipMemcpy(thr, dt.p, sizeof(uint32_t) * (size_t)g->ne, hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(alias, da.p, sizeof(int32_t) * (size_t)g->ne, hipMemcpyDeviceToHost));
@@ -555,14 +562,14 @@ int fw_graph_build_alias(fw_graph *g, void *stream)
     const size_t ne = (size_t)(g->ne > 0 ? g->ne : 1);
     const size_t rec = 16 * (size_t)fw::kPropU4;
     uint4 *prop = nullptr;
-    if (hipMalloc((void **)&prop, rec * ne) != hipSuccess)
+    if (pool_malloc(&prop, rec * ne) != hipSuccess)
         return fail(FW_E_NOMEM, "fw_graph_build_alias: hipMalloc of %zu bytes failed", rec * ne);
     DevBuf val, idx, rowinfo, hubs, nhub;
     const size_t nv = (size_t)(g->nv > 0 ? g->nv : 1);
-    if (hipMalloc(&val.p, 16 * ne) != hipSuccess || hipMalloc(&idx.p, 4 * ne) != hipSuccess ||
-        hipMalloc(&rowinfo.p, 16 * nv) != hipSuccess || hipMalloc(&hubs.p, 4 * nv) != hipSuccess ||
-        hipMalloc(&nhub.p, sizeof(int)) != hipSuccess) {
-        (void)hipFree(prop);
+    if (pool_malloc(&val.p, 16 * ne) != hipSuccess || pool_malloc(&idx.p, 4 * ne) != hipSuccess ||
+        pool_malloc(&rowinfo.p, 16 * nv) != hipSuccess || pool_malloc(&hubs.p, 4 * nv) != hipSuccess ||
+        fw::dev_malloc(&nhub.p, sizeof(int)) != hipSuccess) {
+        fw::dev_pool().free(prop, false);
         return fail(FW_E_NOMEM, "fw_graph_build_alias: scratch of %zu bytes failed", 20 * ne + 20 * nv);
     }
     hipStream_t s = (hipStream_t)stream;
@@ -574,8 +581,9 @@ int fw_graph_build_alias(fw_graph *g, void *stream)
                                    (int32_t *)idx.p, (ulonglong2 *)rowinfo.p, (int32_t *)hubs.p, (int *)nhub.p, prop,
                                    s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess) val.unused = idx.unused = rowinfo.unused = hubs.unused = true;
     if (e != hipSuccess) {
-        (void)hipFree(prop);
+        fw::dev_pool().free(prop, false);
         return fail(FW_E_DEVICE, "fw_graph_build_alias: %s", hipGetErrorString(e));
     }
     g->prop = prop;
@@ -597,7 +605,7 @@ int fw_graph_build_label_alias(fw_graph *g, void *stream)
     int mx = 0;
     {
         DevBuf d;
-        HIP_TRY(hipMalloc(&d.p, sizeof(int)));
+        HIP_TRY(fw::dev_malloc(&d.p, sizeof(int)));
         HIP_TRY(hipMemsetAsync(d.p, 0, sizeof(int), s));
         HIP_TRY(fw::launch_label_max(g->label, g->ne, (int *)d.p, s));
         HIP_TRY(hipMemcpyAsync(&mx, d.p, sizeof(int), hipMemcpyDeviceToHost, s));
@@ -613,22 +621,22 @@ int fw_graph_build_label_alias(fw_graph *g, void *stream)
     int64_t *lrow = nullptr;
     uint4 *lprop = nullptr;
     // (whole 16-byte parts, as the walk reads them)
-    if (hipMalloc((void **)&lrow, 16 * (ng / 2 + 2)) != hipSuccess) {
+    if (pool_malloc(&lrow, 16 * (ng / 2 + 2)) != hipSuccess) {
         return fail(FW_E_NOMEM, "fw_graph_build_label_alias: hipMalloc of %zu bytes failed", 8 * (ng + 1));
     }
-    if (hipMalloc((void **)&lprop, rec * ne) != hipSuccess) {
-        (void)hipFree(lrow);
+    if (pool_malloc(&lprop, rec * ne) != hipSuccess) {
+        fw::dev_pool().free(lrow, false);
         return fail(FW_E_NOMEM, "fw_graph_build_label_alias: hipMalloc of %zu bytes failed", rec * ne);
     }
     DevBuf gmax, vcol, vh, vlab, val, idx, rowinfo, hubs, nhub;
     const size_t ngr = ng > 0 ? ng : 1;
-    if (hipMalloc(&gmax.p, 4 * ngr) != hipSuccess || hipMalloc(&vcol.p, 4 * ne) != hipSuccess ||
-        (g->h && hipMalloc(&vh.p, 4 * ne) != hipSuccess) || hipMalloc(&vlab.p, ne) != hipSuccess ||
-        hipMalloc(&val.p, 16 * ne) != hipSuccess || hipMalloc(&idx.p, 4 * ne) != hipSuccess ||
-        hipMalloc(&rowinfo.p, 16 * ngr) != hipSuccess || hipMalloc(&hubs.p, 4 * ngr) != hipSuccess ||
-        hipMalloc(&nhub.p, sizeof(int)) != hipSuccess) {
-        (void)hipFree(lrow);
-        (void)hipFree(lprop);
+    if (pool_malloc(&gmax.p, 4 * ngr) != hipSuccess || pool_malloc(&vcol.p, 4 * ne) != hipSuccess ||
+        (g->h && pool_malloc(&vh.p, 4 * ne) != hipSuccess) || pool_malloc(&vlab.p, ne) != hipSuccess ||
+        pool_malloc(&val.p, 16 * ne) != hipSuccess || pool_malloc(&idx.p, 4 * ne) != hipSuccess ||
+        pool_malloc(&rowinfo.p, 16 * ngr) != hipSuccess || pool_malloc(&hubs.p, 4 * ngr) != hipSuccess ||
+        fw::dev_malloc(&nhub.p, sizeof(int)) != hipSuccess) {
+        fw::dev_pool().free(lrow, false);
+        fw::dev_pool().free(lprop, false);
         return fail(FW_E_NOMEM, "fw_graph_build_label_alias: scratch of %zu bytes failed", 29 * ne + 24 * ngr);
     }
     const int64_t total = g->ne;
@@ -644,9 +652,11 @@ int fw_graph_build_label_alias(fw_graph *g, void *stream)
                                    (int64_t)ng, g->ne, g->vrec, (const float *)gmax.p, (uint4 *)val.p, (int32_t *)idx.p,
                                    (ulonglong2 *)rowinfo.p, (int32_t *)hubs.p, (int *)nhub.p, lprop, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
+    if (e == hipSuccess)
+        for (DevBuf *b : {&gmax, &vcol, &vh, &vlab, &val, &idx, &rowinfo, &hubs}) b->unused = true;
     if (e != hipSuccess) {
-        (void)hipFree(lrow);
-        (void)hipFree(lprop);
+        fw::dev_pool().free(lrow, false);
+        fw::dev_pool().free(lprop, false);
         return fail(FW_E_DEVICE, "fw_graph_build_label_alias: %s", hipGetErrorString(e));
     }
     g->lrow = lrow;
@@ -662,8 +672,8 @@ int fw_calibrate_random_reads(int64_t bytes, double *reads_per_s, void *stream)
         return fail(FW_E_INVALID, "fw_calibrate_random_reads: bytes must be a power of two >= 1 MiB");
     hipStream_t s = (hipStream_t)stream;
     DevBuf arr, sink;
-    HIP_TRY(hipMalloc(&arr.p, (size_t)bytes));
-    HIP_TRY(hipMalloc(&sink.p, sizeof(unsigned)));
+    HIP_TRY(fw::dev_malloc(&arr.p, (size_t)bytes));
+    HIP_TRY(fw::dev_malloc(&sink.p, sizeof(unsigned)));
     HIP_TRY(hipMemsetAsync(arr.p, 1, (size_t)bytes, s));
     const uint64_t mask = (uint64_t)bytes / 8 - 1;
     const int blocks = 4096, rounds = 64;
@@ -704,7 +714,7 @@ int fw_plan_profile(fw_graph *g, const fw_logic *lg, fw_plan *out, void *stream)
     std::vector<int2> cand((size_t)ncand);
     {
         DevBuf d_cand;
-        HIP_TRY(hipMalloc(&d_cand.p, sizeof(int2) * cand.size()));
+        HIP_TRY(fw::dev_malloc(&d_cand.p, sizeof(int2) * cand.size()));
         HIP_TRY(fw::launch_profile_pick(g->row_ptr, stride, (int)ncand, (int2 *)d_cand.p, s));
         HIP_TRY(hipMemcpyAsync(cand.data(), d_cand.p, sizeof(int2) * cand.size(), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -724,8 +734,8 @@ int fw_plan_profile(fw_graph *g, const fw_logic *lg, fw_plan *out, void *stream)
     fill_args(g, lg, a);
     a.q0.key0 = 0x5eed;
     DevBuf d_nodes, d_sink;
-    HIP_TRY(hipMalloc(&d_nodes.p, sizeof(int32_t) * nodes.size()));
-    HIP_TRY(hipMalloc(&d_sink.p, sizeof(float)));
+    HIP_TRY(fw::dev_malloc(&d_nodes.p, sizeof(int32_t) * nodes.size()));
+    HIP_TRY(fw::dev_malloc(&d_sink.p, sizeof(float)));
     HIP_TRY(hipMemcpy(d_nodes.p, nodes.data(), sizeof(int32_t) * nodes.size(), hipMemcpyHostToDevice));
     Events ev;
     HIP_TRY(hipEventCreate(&ev.a));
@@ -789,9 +799,9 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
         starts[(size_t)i] = (int32_t)(x % (uint64_t)g->nv);
     }
     DevBuf d_starts, d_paths, d_len;
-    HIP_TRY(hipMalloc(&d_starts.p, sizeof(int32_t) * (size_t)n));
-    HIP_TRY(hipMalloc(&d_paths.p, sizeof(int32_t) * (size_t)(nq * n * (L + 1))));
-    HIP_TRY(hipMalloc(&d_len.p, sizeof(int32_t) * (size_t)(nq * n)));
+    HIP_TRY(fw::dev_malloc(&d_starts.p, sizeof(int32_t) * (size_t)n));
+    HIP_TRY(fw::dev_malloc(&d_paths.p, sizeof(int32_t) * (size_t)(nq * n * (L + 1))));
+    HIP_TRY(fw::dev_malloc(&d_len.p, sizeof(int32_t) * (size_t)(nq * n)));
     HIP_TRY(hipMemcpy(d_starts.p, starts.data(), sizeof(int32_t) * (size_t)n, hipMemcpyHostToDevice));
     Events ev;
     HIP_TRY(hipEventCreate(&ev.a));
@@ -1043,8 +1053,8 @@ int fw_batch_create(fw_graph *g, const fw_query *qs, int64_t nq, const fw_plan *
     HIP_TRY(hipSetDevice(g->device));
     fw_batch *b = new fw_batch();
     b->g = g;
-    if (hipMalloc((void **)&b->d_queries, sizeof(fw::QueryDev) * tab.size()) != hipSuccess ||
-        hipMalloc((void **)&b->d_queue, fw::kQueueWords * sizeof(unsigned long long)) != hipSuccess) {
+    if (fw::dev_malloc(&b->d_queries, sizeof(fw::QueryDev) * tab.size()) != hipSuccess ||
+        fw::dev_malloc(&b->d_queue, fw::kQueueWords * sizeof(unsigned long long)) != hipSuccess) {
         batch_free(b);
         return fail(FW_E_NOMEM, "fw_batch_create: hipMalloc failed");
     }

@@ -28,6 +28,7 @@
 #include <vector>
 
 #include "fw_host.h"
+#include "fw_pool.h"
 
 namespace {
 
@@ -391,11 +392,11 @@ int fw_server_create(fw_graph *g, const fw_plan *plan, int32_t strategy, uint64_
     s->max_pending = max_pending;
     s->budget = (size_t)hbm_budget;
     for (int32_t i = max_active - 1; i >= 0; --i) s->free_slots.push_back(i);
-    if (hipMalloc((void **)&s->arena_base, s->budget) != hipSuccess ||
-        hipMalloc((void **)&s->d_done, sizeof(int32_t) * (size_t)max_active) != hipSuccess ||
-        hipMalloc((void **)&s->d_table, sizeof(fw::QueryDev) * kGroups * (size_t)max_active) != hipSuccess ||
-        hipMalloc((void **)&s->d_queue, kGroups * sizeof(unsigned long long)) != hipSuccess ||
-        hipMalloc((void **)&s->d_stats, FW_NSTATS * sizeof(unsigned long long)) != hipSuccess ||
+    if (fw::dev_malloc(&s->arena_base, s->budget) != hipSuccess ||
+        fw::dev_malloc(&s->d_done, sizeof(int32_t) * (size_t)max_active) != hipSuccess ||
+        fw::dev_malloc(&s->d_table, sizeof(fw::QueryDev) * kGroups * (size_t)max_active) != hipSuccess ||
+        fw::dev_malloc(&s->d_queue, kGroups * sizeof(unsigned long long)) != hipSuccess ||
+        fw::dev_malloc(&s->d_stats, FW_NSTATS * sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc((void **)&s->h_table, sizeof(fw::QueryDev) * kGroups * (size_t)max_active, hipHostMallocDefault) !=
             hipSuccess ||
         hipHostMalloc((void **)&s->h_done, sizeof(int32_t) * (size_t)max_active, hipHostMallocDefault) != hipSuccess) {

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import synth
-from tests._gpu import GpuGraph, fw_logic, fw_plan, gpu_walk
+from tests._gpu import GpuGraph, assert_parity, gpu_walk, parity
 
 import paper_2512_00705_amd as fw
 
@@ -146,3 +146,39 @@ def test_alias_tables_of_row_lengths(lens, weights):
     othr, oal = oracle.Graph(g).alias()
     np.testing.assert_array_equal(al, oal)
     np.testing.assert_array_equal(thr, othr)
+
+
+def test_graphs_one_after_another():
+    """Graphs of changing sizes from several threads at once, created, built, walked and destroyed
+    in turn (their memory is kept for the next ones, at most 8 GiB of it): every walk equals the
+    oracle's, whatever the blocks held before."""
+    import threading
+
+    lg, pl = oracle.Logic(kind=oracle.NODE2VEC, weighted=True, p=4.0, q=0.25), oracle.Plan(rho=1.0, proposal=1)
+    cases = []
+    for scale, seed in ((13, 1), (15, 2), (14, 3), (15, 4)):
+        g = synth.rmat(scale, 12 << scale, seed=seed)
+        starts = np.arange(0, g["nv"], 97, dtype=np.int32)
+        cases.append((g, starts, oracle.walk(oracle.Graph(g), lg, pl, oracle.AUTO, starts, 12, seed)))
+    free0 = torch.cuda.mem_get_info()[0]
+    done = []
+
+    def work(first):
+        for i in range(10):
+            g, starts, want = cases[(first + i) % len(cases)]
+            gg = GpuGraph(g, index=bool(i % 2), alias=True)
+            try:
+                p, ln, _ = gpu_walk(gg, lg, pl, oracle.AUTO, starts, 12, 1 + (first + i) % len(cases))
+            finally:
+                gg.close()
+            done.append(parity(p, ln, want))
+
+    threads = [threading.Thread(target=work, args=(k,)) for k in range(3)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert len(done) == 30
+    for rep in done:
+        assert_parity(rep)
+    assert free0 - torch.cuda.mem_get_info()[0] < (9 << 30)
