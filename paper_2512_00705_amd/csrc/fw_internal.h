@@ -158,13 +158,20 @@ int trial_blocks_node2vec(bool weighted, bool batch, int proposal, int ev, int l
 int trial_blocks_secondpr(bool weighted, bool batch, int proposal, int ev, int lds_cap);
 int trial_blocks_metapath(bool weighted, bool batch, int proposal, int ev, int lds_cap);
 hipError_t launch_zero(unsigned long long *p, int n, hipStream_t s);
-hipError_t launch_fill_i32(int32_t *p, int64_t n, int32_t v, hipStream_t s);
 // 8-bit weights: h[k] = h_scale * code[k] (float32 product) for k < ne.
 hipError_t launch_dequantize(const uint8_t *code, float h_scale, int64_t ne, float *h, hipStream_t s);
 // 8-bit weights: erec8[k] = col[k] | code[k] << 24 for k < ne (every col < 2^24).
 hipError_t launch_pack8(const int32_t *col, const uint8_t *code, int64_t ne, uint32_t *erec8, hipStream_t s);
 hipError_t launch_layout(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int64_t ne,
                          uint2 *edges, uint4 *vrec, uint32_t *start_hi, hipStream_t s);
+// One copy of launch_moves: words 4-byte words from src, or zeros when src is null.
+struct MoveDev {
+    const int32_t *src;
+    int32_t *dst;
+    int64_t words;
+};
+// Carries out n moves (the table and any address in device memory or pinned host memory).
+hipError_t launch_moves(const MoveDev *moves, int n, hipStream_t s);
 hipError_t launch_preprocess(const int64_t *row_ptr, const float *h, int64_t nv, uint4 *vrec, hipStream_t s);
 // Proposal records of h-proportional eRJS: Walker's alias table per row (the sweeping
 // construction in exact integer arithmetic, in parallel form) written as

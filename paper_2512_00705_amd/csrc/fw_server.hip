@@ -9,7 +9,11 @@
 // while others run therefore joins at the next tick and shares every later launch with
 // them.  The results of the requests that finished in a tick are copied out while the
 // next tick runs (a copy stream beside the launch stream; the finished requests' blocks
-// are no longer touched by later launches and are freed once copied).  Walker i of a
+// are no longer touched by later launches and are freed once copied).  Starts, tables and
+// results pass through pinned host memory in two kernels per tick (moves_kernel), one before the
+// launches and one on the copy stream; results stay there until they are asked for.  With a copy
+// call per piece and results in fresh host memory, 30 requests of up to 16384 x 100 steps at
+// scale 20 took 3.97 ms, of which the walks 1.2; now 2.40.  Walker i of a
 // request draws from the request's seed with Philox counter
 // (i, step, draw, tag), so its result is the same alone, in any mix and for any tick
 // length.
@@ -35,6 +39,8 @@ namespace {
 using Clock = std::chrono::steady_clock;
 
 constexpr size_t kAlign = 256;
+// Pinned host memory of a server, at most; what finds no room there goes by copy calls.
+constexpr size_t kPinned = (size_t)32 << 20;
 
 size_t round_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 
@@ -101,7 +107,9 @@ struct Request {
     int64_t n = 0;
     int32_t L = 0;
     uint64_t seed = 0;
-    std::vector<int32_t> starts;  // host copy until admitted
+    std::vector<int32_t> starts;  // host copy until finished, when pinned memory has no room
+    size_t p_starts = 0, p_starts_bytes = 0;  // else its place there
+    size_t p_res = 0, p_res_bytes = 0;        // the results' place there: paths | lengths
     size_t off = 0, bytes = 0;    // device block: starts | lengths | prog | paths
     size_t o_starts = 0, o_len = 0, o_prog = 0, o_paths = 0;
     int32_t slot = -1;
@@ -140,6 +148,9 @@ struct fw_server {
     unsigned long long *d_queue = nullptr;     // one walker counter per group
     unsigned long long *d_stats = nullptr;     // FW_NSTATS counters
     int32_t *h_done = nullptr;                 // pinned copy of d_done after each tick
+    fw::MoveDev *h_moves = nullptr;            // pinned: a tick's moves in, then those out
+    char *pin = nullptr;                       // pinned memory for starts and results (null: none)
+    Arena pin_arena;                           // its blocks (under mu)
     std::vector<int32_t> free_slots;
 
     std::mutex mu;
@@ -200,15 +211,25 @@ void pick(fw_server *s, std::vector<Request *> &out)
     }
 }
 
-// Upload the picked requests' starts, clear their progress and done counters.
-int admit(fw_server *s, std::vector<Request *> &picked)
+size_t result_bytes(const Request *r)
+{
+    return round_up(sizeof(int32_t) * (size_t)r->n * ((size_t)r->L + 1)) + sizeof(int32_t) * (size_t)r->n;
+}
+
+size_t result_lengths(const Request *r) { return round_up(sizeof(int32_t) * (size_t)r->n * ((size_t)r->L + 1)); }
+
+// The picked requests' starts go up, their progress and done counters to zero: moves for the
+// tick's first kernel, which `tick` launches.
+int admit(fw_server *s, std::vector<Request *> &picked, int &moves)
 {
     for (Request *r : picked) {
-        if (r->n > 0)
+        if (r->p_starts_bytes > 0)
+            s->h_moves[moves++] = {(const int32_t *)(s->pin + r->p_starts), (int32_t *)(s->arena_base + r->o_starts), r->n};
+        else if (r->n > 0)
             SRV_TRY(hipMemcpyAsync(s->arena_base + r->o_starts, r->starts.data(), sizeof(int32_t) * (size_t)r->n,
                                    hipMemcpyHostToDevice, s->stream));
-        SRV_TRY(fw::launch_fill_i32((int32_t *)(s->arena_base + r->o_prog), r->n, 0, s->stream));
-        SRV_TRY(fw::launch_fill_i32(s->d_done + r->slot, 1, 0, s->stream));
+        s->h_moves[moves++] = {nullptr, (int32_t *)(s->arena_base + r->o_prog), r->n};
+        s->h_moves[moves++] = {nullptr, s->d_done + r->slot, 1};
         r->state = 1;
         s->active.push_back(r);
     }
@@ -219,23 +240,26 @@ int admit(fw_server *s, std::vector<Request *> &picked)
     return FW_OK;
 }
 
-// One tick: a batched launch per group of admitted requests, then the done counters' copy
-// and an event (nothing waits here; tick_wait does).
-int tick(fw_server *s)
+// One tick: the moves in, a batched launch per group of admitted requests, then the done
+// counters' copy and an event (nothing waits here; tick_wait does).
+int tick(fw_server *s, int moves)
 {
-    for (int grp = 0; grp < kGroups; ++grp) {
-        const int kind = 1 + grp / 2;  // FW_NODE2VEC, FW_METAPATH, FW_SECOND_PR
-        const bool weighted_logic = (grp & 1) != 0;
-        fw::QueryDev *tab = s->h_table + (size_t)grp * s->max_active;
+    struct Group {
         int32_t nq = 0;
         int64_t total = 0;
         int ev = fw::kEvNone;
         const fw_logic *lg0 = nullptr;
+    } groups[kGroups];
+    for (int grp = 0; grp < kGroups; ++grp) {
+        const int kind = 1 + grp / 2;  // FW_NODE2VEC, FW_METAPATH, FW_SECOND_PR
+        const bool weighted_logic = (grp & 1) != 0;
+        fw::QueryDev *tab = s->h_table + (size_t)grp * s->max_active;
+        Group &p = groups[grp];
         for (Request *r : s->active) {
             if (r->logic.kind != kind || (r->logic.weighted != 0) != weighted_logic) continue;
-            fw::QueryDev &d = tab[nq++];
+            fw::QueryDev &d = tab[p.nq++];
             fw::host::fill_query(&r->logic, d);
-            d.first = total;
+            d.first = p.total;
             d.n = r->n;
             d.starts = (const int32_t *)(s->arena_base + r->o_starts);
             d.paths = (int32_t *)(s->arena_base + r->o_paths);
@@ -245,25 +269,31 @@ int tick(fw_server *s)
             d.L = r->L;
             d.key0 = (uint32_t)r->seed;
             d.key1 = (uint32_t)(r->seed >> 32);
-            total += r->n;
-            lg0 = &r->logic;
-            ev = std::max(ev, fw::host::ev_of(&s->plan, s->strategy, lg0));
+            p.total += r->n;
+            p.lg0 = &r->logic;
+            p.ev = std::max(p.ev, fw::host::ev_of(&s->plan, s->strategy, p.lg0));
         }
-        if (total == 0) continue;
-        fw::QueryDev *dtab = s->d_table + (size_t)grp * s->max_active;
-        SRV_TRY(hipMemcpyAsync(dtab, tab, sizeof(fw::QueryDev) * (size_t)nq, hipMemcpyHostToDevice, s->stream));
+        if (p.total > 0)
+            s->h_moves[moves++] = {(const int32_t *)tab, (int32_t *)(s->d_table + (size_t)grp * s->max_active),
+                                   (int64_t)(sizeof(fw::QueryDev) / sizeof(int32_t)) * p.nq};
+    }
+    // (the last tick has been waited for, so its moves and tables are no longer read)
+    SRV_TRY(fw::launch_moves(s->h_moves, moves, s->stream));
+    for (int grp = 0; grp < kGroups; ++grp) {
+        const Group &p = groups[grp];
+        if (p.total == 0) continue;
         fw::WalkArgs a;
-        fw::host::fill_args(s->g, lg0, a);
+        fw::host::fill_args(s->g, p.lg0, a);
         fw::host::plan_args(&s->plan, s->strategy, a);
-        a.n = total;
+        a.n = p.total;
         a.queue = s->d_queue + grp;
         a.err = (int *)(s->g->scratch + 1);
         a.stats = s->d_stats;
-        a.queries = dtab;
-        a.nq = nq;
+        a.queries = s->d_table + (size_t)grp * s->max_active;
+        a.nq = p.nq;
         a.tick_steps = s->tick_steps;
-        const bool weighted = weighted_logic && s->g->h;
-        SRV_TRY(fw::launch_walk(a, fw::walk_shape(a, kind, weighted, true, ev, total, s->plan.grid), s->stream));
+        const bool weighted = (grp & 1) != 0 && s->g->h;
+        SRV_TRY(fw::launch_walk(a, fw::walk_shape(a, 1 + grp / 2, weighted, true, p.ev, p.total, s->plan.grid), s->stream));
     }
     SRV_TRY(hipMemcpyAsync(s->h_done, s->d_done, sizeof(int32_t) * (size_t)s->max_active, hipMemcpyDeviceToHost,
                            s->stream));
@@ -290,21 +320,36 @@ int tick_wait(fw_server *s)
 int retire(fw_server *s)
 {
     if (s->done_tick.empty()) return FW_OK;
+    fw::MoveDev *const out = s->h_moves + 3 * (size_t)s->max_active + kGroups;
+    int moves = 0;
     for (Request *r : s->done_tick) {
-        r->paths.resize((size_t)r->n * ((size_t)r->L + 1));
-        r->lengths.resize((size_t)r->n);
-        if (r->n > 0) {
-            SRV_TRY(hipMemcpyAsync(r->paths.data(), s->arena_base + r->o_paths, sizeof(int32_t) * r->paths.size(),
-                                   hipMemcpyDeviceToHost, s->cstream));
-            SRV_TRY(hipMemcpyAsync(r->lengths.data(), s->arena_base + r->o_len, sizeof(int32_t) * r->lengths.size(),
-                                   hipMemcpyDeviceToHost, s->cstream));
+        if (r->n == 0) continue;
+        {
+            std::lock_guard<std::mutex> lk(s->mu);
+            if (s->pin && s->pin_arena.alloc(result_bytes(r), &r->p_res)) r->p_res_bytes = result_bytes(r);
         }
+        const int64_t slots = r->n * ((int64_t)r->L + 1);
+        if (r->p_res_bytes > 0) {
+            out[moves++] = {(const int32_t *)(s->arena_base + r->o_paths), (int32_t *)(s->pin + r->p_res), slots};
+            out[moves++] = {(const int32_t *)(s->arena_base + r->o_len),
+                            (int32_t *)(s->pin + r->p_res + result_lengths(r)), r->n};
+            continue;
+        }
+        r->paths.resize((size_t)slots);
+        r->lengths.resize((size_t)r->n);
+        SRV_TRY(hipMemcpyAsync(r->paths.data(), s->arena_base + r->o_paths, sizeof(int32_t) * r->paths.size(),
+                               hipMemcpyDeviceToHost, s->cstream));
+        SRV_TRY(hipMemcpyAsync(r->lengths.data(), s->arena_base + r->o_len, sizeof(int32_t) * r->lengths.size(),
+                               hipMemcpyDeviceToHost, s->cstream));
     }
+    SRV_TRY(fw::launch_moves(out, moves, s->cstream));
     SRV_TRY(hipStreamSynchronize(s->cstream));
     std::lock_guard<std::mutex> lk(s->mu);
     const auto now = Clock::now();
     for (Request *r : s->done_tick) {
         s->arena.release(r->off, r->bytes);
+        s->pin_arena.release(r->p_starts, r->p_starts_bytes);
+        r->p_starts_bytes = 0;
         s->free_slots.push_back(r->slot);
         r->slot = -1;
         r->state = 2;
@@ -335,9 +380,10 @@ void serve(fw_server *s)
                 continue;
             }
         }
-        if (admit(s, picked) != FW_OK) break;
+        int moves = 0;
+        if (admit(s, picked, moves) != FW_OK) break;
         const bool launched = !s->active.empty();
-        if (launched && tick(s) != FW_OK) break;
+        if (launched && tick(s, moves) != FW_OK) break;
         // the last tick's finished requests are copied out while this one runs
         if (retire(s) != FW_OK) break;
         if (launched && tick_wait(s) != FW_OK) break;
@@ -352,6 +398,8 @@ void server_free(fw_server *s)
     if (s->cstream) (void)hipStreamDestroy(s->cstream);
     if (s->ev_tick) (void)hipEventDestroy(s->ev_tick);
     if (s->h_done) (void)hipHostFree(s->h_done);
+    if (s->h_moves) (void)hipHostFree(s->h_moves);
+    if (s->pin) (void)hipHostFree(s->pin);
     (void)hipFree(s->arena_base);
     (void)hipFree(s->d_done);
     (void)hipFree(s->d_table);
@@ -399,11 +447,21 @@ int fw_server_create(fw_graph *g, const fw_plan *plan, int32_t strategy, uint64_
         fw::dev_malloc(&s->d_stats, FW_NSTATS * sizeof(unsigned long long)) != hipSuccess ||
         hipHostMalloc((void **)&s->h_table, sizeof(fw::QueryDev) * kGroups * (size_t)max_active, hipHostMallocDefault) !=
             hipSuccess ||
-        hipHostMalloc((void **)&s->h_done, sizeof(int32_t) * (size_t)max_active, hipHostMallocDefault) != hipSuccess) {
+        hipHostMalloc((void **)&s->h_done, sizeof(int32_t) * (size_t)max_active, hipHostMallocDefault) != hipSuccess ||
+        hipHostMalloc((void **)&s->h_moves, sizeof(fw::MoveDev) * (5 * (size_t)max_active + kGroups),
+                      hipHostMallocDefault) != hipSuccess) {
         server_free(s);
         return fail(FW_E_NOMEM, "fw_server_create: allocation failed");
     }
     s->arena.reset(s->budget);
+    const size_t pin = std::min(s->budget, kPinned);
+    if (hipHostMalloc((void **)&s->pin, pin, hipHostMallocDefault) == hipSuccess) {
+        memset(s->pin, 0, pin);  // (mapped now, not page by page under the first requests)
+        s->pin_arena.reset(pin);
+    } else {
+        (void)hipGetLastError();
+        s->pin = nullptr;  // copies go piece by piece
+    }
     if (hipStreamCreateWithFlags(&s->stream, hipStreamNonBlocking) != hipSuccess ||
         hipStreamCreateWithFlags(&s->cstream, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&s->ev_tick, hipEventDisableTiming) != hipSuccess ||
@@ -445,7 +503,12 @@ int fw_server_submit(fw_server *s, const fw_logic *logic, const int32_t *starts,
     r->L = L;
     r->seed = seed;
     r->bytes = bytes;
-    r->starts.assign(starts, starts + n);
+    if (n > 0 && s->pin && s->pin_arena.alloc(sizeof(int32_t) * (size_t)n, &r->p_starts)) {
+        r->p_starts_bytes = sizeof(int32_t) * (size_t)n;
+        memcpy(s->pin + r->p_starts, starts, r->p_starts_bytes);
+    } else {
+        r->starts.assign(starts, starts + n);
+    }
     r->t_submit = Clock::now();
     s->reqs[r->id] = r;
     s->waiting.push_back(r);
@@ -479,6 +542,12 @@ int fw_server_result(fw_server *s, uint64_t req_id, int32_t *paths, int32_t *len
     if (it == s->reqs.end()) return fail(FW_E_INVALID, "fw_server_result: unknown request %llu", (unsigned long long)req_id);
     Request *r = it->second;
     if (r->state != 2) return fail(FW_E_STATE, "fw_server_result: request %llu not finished", (unsigned long long)req_id);
+    if (r->p_res_bytes > 0) {
+        const char *res = s->pin + r->p_res;
+        if (paths) memcpy(paths, res, sizeof(int32_t) * (size_t)r->n * ((size_t)r->L + 1));
+        if (lengths) memcpy(lengths, res + result_lengths(r), sizeof(int32_t) * (size_t)r->n);
+        s->pin_arena.release(r->p_res, r->p_res_bytes);
+    }
     if (paths && !r->paths.empty()) memcpy(paths, r->paths.data(), sizeof(int32_t) * r->paths.size());
     if (lengths && !r->lengths.empty()) memcpy(lengths, r->lengths.data(), sizeof(int32_t) * r->lengths.size());
     if (latency_s) *latency_s = std::chrono::duration<double>(r->t_done - r->t_submit).count();

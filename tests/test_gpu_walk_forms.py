@@ -113,3 +113,33 @@ def test_path_parts_at_every_alignment(L):
                           {"unflagged": [] if (p[:, 0] == starts).all() else ["start"], "flagged": [], "steps": 1})
     finally:
         gg.close()
+
+
+def test_served_results_with_and_without_pinned_room():
+    """Results and starts that find room in the server's 32 MiB of pinned memory and those that do
+    not (nothing is fetched before all are done): odd sizes, single walkers, paths of one slot."""
+    g = _graph(False)
+    gg = GpuGraph(g, alias=True, index=True)
+    pl = oracle.Plan(rho=1.0, proposal=1)
+    rng = np.random.default_rng(11)
+    jobs = [(int(n), int(L), 50 + i) for i, (n, L) in enumerate(
+        [(1, 1), (3, 0), (60001, 40), (1, 100), (70003, 39), (5, 7), (90001, 31), (0, 5), (64, 3), (80000, 33), (2, 2)])]
+    try:
+        srv = fw.fw_server_create(gg.handle, fw_plan(pl), fw.FW_AUTO, 1 << 28, 16, 8, 64)
+        try:
+            sent = {}
+            for n, L, seed in jobs:
+                st = rng.integers(0, g["nv"], n).astype(np.int32)
+                sent[fw.fw_server_submit(srv, fw_logic(N2V), st, L, seed)] = (st, n, L, seed)
+            left = set(sent)
+            while left:
+                left.discard(fw.fw_server_next_done(srv, 1000))
+            got = {i: fw.fw_server_result(srv, i, n, L)[:2] for i, (st, n, L, seed) in sent.items()}
+        finally:
+            fw.fw_server_destroy(srv)
+        for i, (st, n, L, seed) in sent.items():
+            p, ln, _ = gpu_walk(gg, N2V, pl, oracle.AUTO, st, L, seed, counters=False)
+            np.testing.assert_array_equal(got[i][0].reshape(n, L + 1), p)
+            np.testing.assert_array_equal(got[i][1], ln)
+    finally:
+        gg.close()
