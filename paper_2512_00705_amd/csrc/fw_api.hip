@@ -406,6 +406,7 @@ void fw::host::fill_args(const fw_graph *g, const fw_logic *lg, fw::WalkArgs &a)
     a.col = g->col;
     a.label = g->label;
     a.nv = g->nv;
+    a.ne = g->ne;
     a.mtab = (const uint4 *)g->mtab;
     a.mtab_mask = g->mtab_mask;
     a.prop = g->prop;

@@ -98,7 +98,7 @@ struct WalkArgs {
     const uint32_t *start_hi;
     const int32_t *col;
     const uint8_t *label;
-    int64_t nv;
+    int64_t nv, ne;
 
     int64_t n;                  // walkers in the launch (all queries)
     unsigned long long *stats;  // may be null
@@ -112,7 +112,7 @@ struct WalkArgs {
     int32_t strategy;
     int32_t lds_cap;
     int32_t item_bytes;         // col (+ h) (+ label) per scanned or proposed edge
-    int32_t wave_lanes;         // lanes of each wave that take walkers (set by launch_walk from n and the grid)
+    int32_t wave_lanes;         // rvs_kernel: lanes of each wave that take walkers (set by launch_walk)
     // walk_kernel (set by launch_walk): the first static_n walkers are shared out over the first
     // static_waves waves, static_each to each and one more to the first static_more
     int64_t static_n, static_waves, static_each, static_more;

@@ -47,9 +47,8 @@ __global__ void __launch_bounds__(kBlock, (STATS || HV > 1) ? kMinWavesCounted :
         if (STATS && __ballot((st[kStTriggers] | st[kStSteps]) > 0x40000000u) != 0) flush_stats(a, st, st_bytes);
 
         // 1. hand walkers to idle lanes: one atomic per wave.  Only the wave's first wave_lanes
-        //    lanes take walkers: a launch of fewer walkers than the grid has lanes spreads them
-        //    over all its waves, since a wave serves its lanes' steps one after another (30001
-        //    walkers of 40 steps at scale 19: 76.0 ms in full waves, 13.5 ms spread).
+        //    lanes take walkers (see launch_walk), since a wave serves its lanes' steps one after
+        //    another.
         const uint64_t idle = __ballot(mode == kIdle) & mine;
         if (idle != 0 && !exhausted) {
             const int leader = __ffsll((unsigned long long)idle) - 1;
@@ -337,7 +336,14 @@ hipError_t launch_walk(const WalkArgs &args, const WalkShape &w, hipStream_t s)
     int ev = w.ev;
     if (ev == kEvNone && a.stats != nullptr) ev = kEvHot;
     const int64_t waves = (int64_t)(rvs_only ? w.grid : w.resident) * kWavesPerBlock;
-    a.wave_lanes = (int32_t)std::min<int64_t>(kWave, (a.n + waves - 1) / waves);
+    // rvs_kernel: walkers spread over all waves, and a wave holds only a quarter of its share at
+    // a time: a walk's cost varies with the rows it meets, and walkers that have not started go to
+    // the waves that are done first.  Rows short enough to be served several at a time (mean below
+    // 12) want more lanes that wait: half.  Full waves, spread whole, by halves, by quarters, in ms:
+    // 30001 x 40 at scale 19: 76.0, 12.8, 10.3, 9.0; MetaPath, 100000 x 20 at scale 18: -, 5.1,
+    // 4.6, 3.9; mean row of 8, 400000 x 5 at scale 14: -, 0.99, 0.94, 1.14.
+    const int64_t share = waves * (a.ne < 12 * a.nv ? 2 : 4);
+    a.wave_lanes = (int32_t)std::min<int64_t>(kWave, (a.n + share - 1) / share);
     // walk_kernel: a launch that the lanes hold whole is shared out over the waves; of a larger
     // one seven eighths, the rest goes by the counter to the waves that are done first
     const bool whole = a.n <= waves * kWave;
