@@ -184,7 +184,9 @@ typedef struct fw_plan {
 int fw_graph_create(const fw_csr *g, fw_graph **out);
 
 /* Free a graph and its device memory.  NULL is accepted.  The caller must ensure no
- * work that uses the graph is still running. */
+ * work that uses the graph is still running.  The library keeps at most 8 GiB of such
+ * memory per process for the next graphs; blocks that eight graphs in a row had no use for
+ * go back to the driver, and all of it when one of the library's allocations fails. */
 int fw_graph_destroy(fw_graph *g);
 
 /* Per-node preprocessing (Section 4.2, preprocess()): h_MAX[v] = max h over N(v) and
@@ -395,7 +397,8 @@ int fw_batch_run_noalloc(fw_graph *g, const fw_query *queries, int64_t nq, const
  * counter (i, step, draw, tag) under the request's seed: results are identical to
  * fw_walk of the same (logic, starts, L, seed), whatever the mix and the tick length.
  * The plan and strategy are fixed for the server's lifetime.  Allocates `hbm_budget`
- * bytes of device memory up front; uses its own stream. */
+ * bytes of device memory up front, and at most 32 MiB of pinned host memory for starts and
+ * results on their way; uses its own streams. */
 typedef struct fw_server fw_server;
 
 int fw_server_create(fw_graph *g, const fw_plan *plan, int32_t strategy, uint64_t hbm_budget,

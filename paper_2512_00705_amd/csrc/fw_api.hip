@@ -1,6 +1,6 @@
 // C ABI of the sampler (include/flexiwalk.h): argument checks, device memory
 // ownership, plan construction and kernel launches.  All sampling runs in
-// fw_kernels.hip.
+// the kernels of fw_trial.h and fw_rvs.hip.
 #include <float.h>
 #include <math.h>
 #include <stdarg.h>
