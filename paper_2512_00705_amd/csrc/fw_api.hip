@@ -937,19 +937,35 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     }
     // eRVS lanes on long rows, for one logic only (hub lanes run in fw_walk launches; a mix
     // is tuned for the batches and servers that take it): P = 128 or 256 on rows of at
-    // least 1024 or 8192 entries; skipped where every step is eRJS, which they change nothing
-    // of, and taken only when clearly faster, since batches and servers refuse them
-    if (n_logics == 1 && ev_of(&bestp, FW_AUTO, &logics[0]) != fw::kEvNone) {
-        const float base = bestt;
-        for (int32_t hl : {128, 256})
-            for (int32_t hd : {1024, 8192}) {
+    // least 1024 or 8192 entries.  Batches and servers refuse such plans, so they are taken only
+    // when some step is eRVS at all and when clearly faster, by 2 %, than both the best plan so
+    // far and the same kernel with no row long enough (which may differ for its registers alone)
+    if (n_logics == 1) {
+        DevBuf d_stats;
+        unsigned long long st[FW_NSTATS];
+        HIP_TRY(fw::dev_malloc(&d_stats.p, sizeof(st)));
+        HIP_TRY(hipMemsetAsync(d_stats.p, 0, sizeof(st), s));
+        rc = fw_walk(g, &logics[0], &bestp, FW_AUTO, (const int32_t *)d_starts.p, n, L, 7, (int32_t *)d_paths.p,
+                     (int32_t *)d_len.p, (uint64_t *)d_stats.p, stream);
+        if (rc != FW_OK) return rc;
+        HIP_TRY(hipMemcpyAsync(st, d_stats.p, sizeof(st), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        if (st[fw::kStRvs] + st[fw::kStFallback] > 0) {
+            const float base = bestt;
+            for (int hl : {128, 256}) {
                 fw_plan p = bestp;
-                p.hub_deg = hd;
                 p.hub_lanes = hl;
-                float t;
-                if ((rc = time_plan(p, &t)) != FW_OK) return rc;
-                if (t < bestt && t < 0.98f * base) bestt = t, bestp = p;
+                p.hub_deg = INT32_MAX;
+                float form;
+                if ((rc = time_plan(p, &form)) != FW_OK) return rc;
+                for (int hd : {1024, 8192}) {
+                    p.hub_deg = hd;
+                    float t;
+                    if ((rc = time_plan(p, &t)) != FW_OK) return rc;
+                    if (t < bestt && t < 0.98f * std::min(base, form)) bestt = t, bestp = p;
+                }
             }
+        }
     }
     // the persistent grid: the occupancy limit (0), half of it, and twice it (blocks past
     // the resident ones start as others finish)
