@@ -42,9 +42,10 @@ constexpr int kPropU4 = 4;
 #define FW_MERGE_RATIO 8
 #endif
 constexpr int kMergeRatio = FW_MERGE_RATIO;  // eRVS merges N(v) with N(prev) while d(prev) <= this * d(v)
-// resident waves per SIMD rvs_kernel is compiled for: 7 without the device counters (no
-// spills), 4 with them or with hub lanes (their extra lane state)
-constexpr int kMinWavesCounted = 4;
+// resident waves per SIMD rvs_kernel is compiled for: 7 without the device counters, 5 with them,
+// 4 with hub lanes (their extra lane state); no vector register spills
+constexpr int kMinWavesHub = 4;
+constexpr int kMinWavesCounted = 5;
 constexpr int kMinWavesRvsOnly = 7;
 
 // How walk_kernel keeps eRVS: kEvNone for plans that send every ordinary step to eRJS (no scan

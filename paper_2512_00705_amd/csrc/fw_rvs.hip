@@ -19,7 +19,7 @@ static size_t rvs_lds_bytes(int lds_cap) { return (size_t)kWavesPerBlock * (size
 // HV: virtual lanes per lane on rows of degree >= hub_deg (P = 64 * HV there); a variant of
 // its own so that the extra lane state costs the other plans no registers.
 template <int KIND, bool W, bool STATS, int HV>
-__global__ void __launch_bounds__(kBlock, (STATS || HV > 1) ? kMinWavesCounted : kMinWavesRvsOnly) rvs_kernel(WalkArgs a)
+__global__ void __launch_bounds__(kBlock, HV > 1 ? kMinWavesHub : STATS ? kMinWavesCounted : kMinWavesRvsOnly) rvs_kernel(WalkArgs a)
 {
     extern __shared__ int32_t lds_all[];
     int32_t *lds = lds_all + (threadIdx.x / kWave) * a.lds_cap;
@@ -238,7 +238,10 @@ __global__ void __launch_bounds__(kBlock, (STATS || HV > 1) ? kMinWavesCounted :
         }
     }
 
-    if (STATS) flush_stats(a, st, st_bytes);
+    if (STATS) {
+        __shared__ uint64_t sums[kWavesPerBlock * kNumStats];
+        flush_stats_block(a, st, st_bytes, sums, kNumStats);
+    }
 }
 
 // ---------------------------------------------------------------- launches

@@ -1076,7 +1076,8 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
         }
     }
 
-    if (STATS) flush_stats(a, st, st_bytes);
+    // (the waves' read slots are free: no lane waits for a read)
+    if (STATS) flush_stats_block(a, st, st_bytes, reinterpret_cast<uint64_t *>(lds_all), kBufU4 * 2);
 }
 
 // The part of a plan's lds_cap that is used (a longer N(prev) is searched in place, as past any

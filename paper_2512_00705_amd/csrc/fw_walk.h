@@ -501,19 +501,54 @@ __device__ __forceinline__ bool rvs_group_pass(const WalkArgs &a, int G, uint64_
     return my_slot >= 0;
 }
 
-// Adds a wave's counters to the device totals and clears them.
-__device__ __forceinline__ void flush_stats(const WalkArgs &a, uint32_t (&cnt)[kStBytes], uint64_t &bytes)
+// A wave's counters summed over its lanes and cleared: lane c gets counter c (lanes from kNumStats
+// on 0).
+__device__ __forceinline__ uint64_t take_stats(uint32_t (&cnt)[kStBytes], uint64_t &bytes)
 {
-    const int lane = lane_id();
+    int lane = lane_id();
+    asm volatile("" : "+v"(lane));  // the masks of the comparisons below are not kept across the walk
+    uint64_t mine = 0;
 #pragma unroll
     for (int c = 0; c < kStBytes; ++c) {
         const uint64_t v = wave_sum_u64(cnt[c]);
-        if (lane == 0 && v != 0) atomicAdd(&a.stats[c], (unsigned long long)v);
+        mine = lane == c ? v : mine;
         cnt[c] = 0;
     }
     const uint64_t b = wave_sum_u64(bytes);
-    if (lane == 0 && b != 0) atomicAdd(&a.stats[kStBytes], (unsigned long long)b);
+    mine = lane == kStBytes ? b : mine;
     bytes = 0;
+    return mine;
+}
+
+// Adds counters (lane c holds counter c) to the device totals, which share one line: one request.
+__device__ __forceinline__ void add_stats(const WalkArgs &a, uint64_t mine)
+{
+    const int lane = lane_id();
+    if (lane < kNumStats && mine != 0) atomicAdd(&a.stats[lane], (unsigned long long)mine);
+}
+
+// Adds a wave's counters to the device totals and clears them.
+__device__ __forceinline__ void flush_stats(const WalkArgs &a, uint32_t (&cnt)[kStBytes], uint64_t &bytes)
+{
+    add_stats(a, take_stats(cnt, bytes));
+}
+
+// The same once per block, at the kernel's end: sums is LDS for the block, kNumStats words per wave
+// at `stride` words.  Every thread of the block calls.  The totals take about 120 M requests a
+// second and a short launch spreads over thousands of waves: with an add per wave and counter
+// 60000 MetaPath walkers x 1 step took 322 us with counters (42 without), now 49.
+__device__ __forceinline__ void flush_stats_block(const WalkArgs &a, uint32_t (&cnt)[kStBytes], uint64_t &bytes,
+                                                  uint64_t *sums, int stride)
+{
+    const int lane = lane_id(), wave = threadIdx.x / kWave;
+    const uint64_t mine = take_stats(cnt, bytes);
+    if (lane < kNumStats) sums[wave * stride + lane] = mine;
+    __syncthreads();
+    if (wave == 0) {
+        uint64_t total = 0;
+        for (int w = 0; w < kWavesPerBlock; ++w) total += lane < kNumStats ? sums[w * stride + lane] : 0;
+        add_stats(a, total);
+    }
 }
 
 }  // namespace fw

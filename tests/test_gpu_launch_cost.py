@@ -1,0 +1,79 @@
+"""What a launch costs beside its walks (needs an MI355X): counters and work hand-out go through
+one address each, which must not set the time of a short launch.  Every bound compares two ways
+to take the same walks on the same device, with room for noise.
+"""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import synth
+from tests._gpu import GpuGraph, fw_logic, fw_plan
+from tests.test_gpu_parity import N2V, MP
+
+import paper_2512_00705_amd as fw
+
+pytestmark = pytest.mark.gpu
+DEV = torch.device("cuda:0")
+
+
+def best_us(f, reps=12):
+    """The fastest of `reps` calls by events, after one that warms up."""
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(reps):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        f()
+        b.record()
+        b.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3)
+    return best
+
+
+class Walks:
+    """fw_walk of n walkers x L steps into buffers of its own."""
+
+    def __init__(self, gg, lg, plan, strategy, n, L, counted=False, seed=5):
+        self.starts = torch.from_numpy(synth.uniform_starts(gg.nv, n, 2)).to(DEV)
+        self.paths = torch.full((n, L + 1), -7, dtype=torch.int32, device=DEV)
+        self.lengths = torch.full((n,), -7, dtype=torch.int32, device=DEV)
+        self.stats = torch.zeros(fw.FW_NSTATS, dtype=torch.int64, device=DEV) if counted else None
+        self.args = (gg.handle, fw_logic(lg), plan, strategy, self.starts, n, L, seed, self.paths, self.lengths,
+                     self.stats)
+
+    def __call__(self):
+        fw.fw_walk(*self.args)
+
+    def out(self):
+        torch.cuda.synchronize()
+        return self.paths.cpu().numpy(), self.lengths.cpu().numpy()
+
+
+def same(a, b):
+    for x, y in zip(a.out(), b.out()):
+        np.testing.assert_array_equal(x, y)
+
+
+@pytest.mark.parametrize("strategy", ["auto", "rvs"])
+def test_counters_of_a_short_launch(strategy):
+    """One step of 60000 walkers with device counters takes less than three times as long as without
+    (with an add per wave and counter: 4 to 8 times)."""
+    print("counters", strategy, flush=True)
+    g = synth.rmat(12, 24 << 12, seed=3, nlabels=5)
+    gg = GpuGraph(g, index=True)
+    try:
+        lg = MP
+        pl = fw_plan(oracle.Plan(rho=0.4, d_lo=32))
+        s = fw.FW_AUTO if strategy == "auto" else fw.FW_RVS_ONLY
+        plain, counted = Walks(gg, lg, pl, s, 60000, 1), Walks(gg, lg, pl, s, 60000, 1, counted=True)
+        t0, t1 = best_us(plain), best_us(counted)
+        same(plain, counted)
+        st = dict(zip(fw.STAT_NAMES, counted.stats.tolist()))
+        assert st["steps"] == 13 * int(plain.lengths.sum().item())  # 13 launches add up
+        assert t1 < 3 * t0, (t0, t1)
+    finally:
+        gg.close()
