@@ -324,9 +324,11 @@ WalkShape walk_shape(const WalkArgs &a, int kind, bool weighted, bool batch, int
     // Never more waves than walkers: few walkers get one lane or a few per wave, since a wave
     // serves its lanes' eRVS steps one after another.  Where every step is eRJS there is nothing
     // to serve, and beyond kSpread waves per SIMD half-empty waves only compete for issue slots.
+    // So do eRVS walks of one step: see launch_walk.
     int64_t need = std::max<int64_t>(1, (n + kWavesPerBlock - 1) / kWavesPerBlock);
-    if (trials_only && (kind == kNode2Vec || a.proposal != 0))
-        need = std::max(std::min(need, (int64_t)cus * kSpread), (n + kBlock - 1) / kBlock);
+    const bool one = !batch && a.strategy == kRvsOnly && a.q0.L <= 1;
+    if (one || (trials_only && (kind == kNode2Vec || a.proposal != 0)))
+        need = std::max(std::min(need, (int64_t)cus * (one ? 1 : kSpread)), (n + kBlock - 1) / kBlock);
     w.grid = plan_grid > 0 ? plan_grid : (int)std::min(full, need);
     w.resident = (int)std::min<int64_t>(full, w.grid);
     return w;
@@ -345,7 +347,11 @@ hipError_t launch_walk(const WalkArgs &args, const WalkShape &w, hipStream_t s)
     // 12) want more lanes that wait: half.  Full waves, spread whole, by halves, by quarters, in ms:
     // 30001 x 40 at scale 19: 76.0, 12.8, 10.3, 9.0; MetaPath, 100000 x 20 at scale 18: -, 5.1,
     // 4.6, 3.9; mean row of 8, 400000 x 5 at scale 14: -, 0.99, 0.94, 1.14.
-    const int64_t share = waves * (a.ne < 12 * a.nv ? 2 : 4);
+    // Walks of one step scan the rows of their starts, which differ little (later steps meet rows in
+    // proportion to their length), and take less than their turn at the counter, which serves about
+    // 120 M a second: up to 64 at a time on a wave per SIMD, then more waves (scale 17, 6000 x 1 and
+    // 300000 x 1: 230 and 734 us by quarters over all waves, now 112 and 268).
+    const int64_t share = a.q0.L <= 1 ? waves : waves * (a.ne < 12 * a.nv ? 2 : 4);
     a.wave_lanes = (int32_t)std::min<int64_t>(kWave, (a.n + share - 1) / share);
     // walk_kernel: a launch that the lanes hold whole is shared out over the waves; of a larger
     // one seven eighths, the rest goes by the counter to the waves that are done first

@@ -77,3 +77,21 @@ def test_counters_of_a_short_launch(strategy):
         assert t1 < 3 * t0, (t0, t1)
     finally:
         gg.close()
+
+
+@pytest.mark.parametrize("n", [6000, 30001, 300000])
+def test_one_step_reservoir_walks(n):
+    """FW_RVS_ONLY walks of one step take less than twice as long as the same walks by the kernel of
+    the other strategies, which hands walkers out without a counter (with a few walkers per add of
+    every wave: 2.5 to 3.5 times)."""
+    print("one step", n, flush=True)
+    g = synth.rmat(17, 16 << 17, seed=3)
+    gg = GpuGraph(g)
+    try:
+        other = Walks(gg, N2V, fw_plan(oracle.Plan(d_lo=1 << 30)), fw.FW_DEGREE_SELECT, n, 1)
+        rvs = Walks(gg, N2V, fw_plan(oracle.Plan()), fw.FW_RVS_ONLY, n, 1)
+        t0, t1 = best_us(other), best_us(rvs)
+        same(other, rvs)
+        assert t1 < 2 * t0, (t0, t1)
+    finally:
+        gg.close()
