@@ -116,7 +116,10 @@ typedef struct fw_logic {
  *            of thr_g), S' = 0; a lane with no threshold yet (-inf) keeps T = 0, and
  *            thr_g >= 0 makes T' = +inf.  Keys below thr_g cannot win, so only fewer
  *            keys are drawn.  A round is P items (hub_lanes on hub rows).
- *   lds_cap  int32 entries of N(prev) staged in LDS per wavefront, 0..8192 (0: never stage)
+ *   lds_cap  int32 entries of N(prev) staged in LDS per wavefront, 0..8192 (0: never stage);
+ *            used up to what finds room without costing the kernel a resident block (1408 in
+ *            eRVS-only launches of one query, 64 to 448 in the others, 1280 with hub lanes); a longer
+ *            N(prev) is read in place
  *   grid     persistent blocks (0 = fill the device)
  *   bound    eRJS bound (changes the stream, never the distribution):
  *            0  max(w) * h_MAX of Section 3.3;

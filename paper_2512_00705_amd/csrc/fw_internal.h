@@ -32,8 +32,7 @@ enum Stat : int {
 
 constexpr int kBlock = 256;          // 4 wavefronts per block, each independent
 constexpr int kWavesPerBlock = kBlock / 64;
-constexpr int kDefaultLdsCap = 512;  // int32 entries of N(prev) per wavefront: with the four 1 KB vertex-record
-                                     // slots a block takes 24 KB, six blocks per CU (1024: 32 KB blocks, slower)
+constexpr int kDefaultLdsCap = 512;  // int32 entries of N(prev) per wavefront, cut to what finds room (fw_lds.h)
 // h-proportional proposal record per CSR entry, 64 bytes (one DRAM line holds it whole):
 //   {col_k, bits(h_k), col_a, bits(h_a)}, {threshold, label_k | label_a << 8, 0, 0},
 //   vrec[col_k], vrec[col_a]  (the candidates' vertex records for the next step's set-up)
@@ -53,7 +52,6 @@ constexpr int kMinWavesRvsOnly = 7;
 // on by a kEvHot launch), kEvHot otherwise, kEvHub with hub lanes (P = 128 or 256 on long rows).
 enum Ev : int { kEvNone = 0, kEvHot = 1, kEvHub = 2 };
 
-constexpr int kHotWaves = 4;    // resident waves per SIMD of the kEvHot form
 constexpr int kQueueWords = 4;  // walker counter, parked flag, the resuming launch's counter, unused
 
 // Per-query constants of a walk job.  Float constants are prepared on the host in float32

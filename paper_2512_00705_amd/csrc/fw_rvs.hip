@@ -9,6 +9,7 @@
 #include <algorithm>
 #include <atomic>
 
+#include "fw_lds.h"
 #include "fw_walk.h"
 
 namespace fw {
@@ -246,8 +247,10 @@ __global__ void __launch_bounds__(kBlock, HV > 1 ? kMinWavesHub : STATS ? kMinWa
 
 // ---------------------------------------------------------------- launches
 template <int KIND, bool W, bool STATS>
-static void launch_rvs_s(const WalkArgs &a, int grid, hipStream_t s)
+static void launch_rvs_s(const WalkArgs &args, int grid, hipStream_t s)
 {
+    WalkArgs a = args;
+    a.lds_cap = rvs_lds_cap(a.lds_cap);
     const size_t lds = rvs_lds_bytes(a.lds_cap);
     const int hv = a.hub_deg > 0 ? a.hub_v : 1;
     if (hv == 4) hipLaunchKernelGGL((rvs_kernel<KIND, W, STATS, 4>), dim3(grid), dim3(kBlock), lds, s, a);
@@ -268,7 +271,7 @@ static int rvs_blocks(int lds_cap)
 {
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&nb, rvs_kernel<KIND, W, false, 1>, kBlock,
-                                                     rvs_lds_bytes(lds_cap)) != hipSuccess)
+                                                     rvs_lds_bytes(rvs_lds_cap(lds_cap))) != hipSuccess)
         nb = 1;
     return nb > 0 ? nb : 1;
 }
@@ -318,7 +321,7 @@ WalkShape walk_shape(const WalkArgs &a, int kind, bool weighted, bool batch, int
     // Counted and resumable launches have no kEvNone form, and one that the kEvHot form's lanes
     // hold whole gains nothing from it and would only pay for the second launch.
     const bool trials_only = ev == kEvNone;
-    if (ev == kEvNone && (a.stats != nullptr || a.tick_steps > 0 || n <= (int64_t)cus * 4 * kHotWaves * kWave)) ev = kEvHot;
+    if (ev == kEvNone && (a.stats != nullptr || a.tick_steps > 0 || n <= (int64_t)cus * 4 * trial_waves(kEvHot) * kWave)) ev = kEvHot;
     WalkShape w{kind, weighted, batch, ev, 1, 1};
     const int64_t full = (int64_t)resident_blocks(a, w) * cus;
     // Never more waves than walkers: few walkers get one lane or a few per wave, since a wave

@@ -20,6 +20,7 @@
 
 #include <algorithm>
 
+#include "fw_lds.h"
 #include "fw_walk.h"
 
 namespace fw {
@@ -54,19 +55,6 @@ enum Res : int {
     kAccP    // ... is prev's
 };
 
-constexpr int kQueryTop = 256;  // entries of the query table's first level in LDS
-
-// Resident waves per SIMD that the kernel is compiled for.  Without the scan its registers
-// spill nothing and LDS holds four blocks per CU; one wave per SIMD already saturates random
-// reads, more only hide the arithmetic between them.
-constexpr int trial_waves(int ev) { return ev == kEvHub ? 3 : 4; }
-
-// Where a wave's reads arrive: 64 slots of 64 bytes, lane l's at (l % 4) * kBufStride + (l / 4) * 4
-// uint4; each quad of lanes fetches its four lanes' slots one after another, its lanes 16 bytes
-// each (see issue_reads).  The stride's extra 16 bytes spread the slots of a quad over the banks.
-constexpr int kBufStride = 65;
-constexpr int kBufU4 = 4 * kBufStride;
-
 // Starts the reads of a pass: lane l wants np 16-byte parts (0..4) from p (aligned to 16).  In
 // round i the four lanes of each quad fetch the parts of the quad's lane i by LDS DMA, so that
 // the wave asks for each line once: four 16-byte loads by the lane itself are four requests
@@ -98,25 +86,7 @@ __device__ __forceinline__ void issue_reads(const uint4 *p, uint32_t np, uint4 *
 #undef FW_ROUND
 }
 
-constexpr bool trial_stash(int kind, int prop) { return uses_membership(kind) && prop == 1; }
-
-// Path slots are held back in LDS until they fill an aligned part of 64 bytes and go out
-// together: a random write of 16 or 32 bytes costs the memory 2.4 times one of 64 (22.8 against
-// 54 G/s alone; random reads beside one write in eight: 33.9 G/s with 16-byte writes, 42.0 with
-// 64-byte writes in proportion).  part_pos(row + s): the place of slot s in its part.
-constexpr int kPart = 16;
 __device__ __forceinline__ uint32_t part_pos(const int32_t *ad) { return ((uint32_t)(uintptr_t)ad >> 2) & (kPart - 1); }
-
-// Dynamic LDS of a block: each wave's read slots, its stash of 64 vertex records (the record of
-// a proposal whose membership test is open) and its held path slots, the schema or the query
-// table's first level, each wave's N(prev) staging area (where the kernel has the scan).
-constexpr size_t trial_lds_bytes(int kind, int prop, bool batch, int ev, int lds_cap)
-{
-    return (size_t)kWavesPerBlock * (kBufU4 * 16 + kWave * kPart * 4) +
-           (trial_stash(kind, prop) ? (size_t)kWavesPerBlock * kWave * 16 : 0) +
-           (batch ? (size_t)kQueryTop * 8 : (kind == kMetaPath ? 64 : 0)) +
-           (uses_membership(kind) && ev != kEvNone ? (size_t)kWavesPerBlock * (size_t)lds_cap * sizeof(int32_t) : 0);
-}
 
 // A value loaded off the pipelined path (rare branches): waited for on the spot, so that no
 // wait for it, which would also wait for the path stores, is left behind the branch.
@@ -1080,25 +1050,13 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
     if (STATS) flush_stats_block(a, st, st_bytes, reinterpret_cast<uint64_t *>(lds_all), kBufU4 * 2);
 }
 
-// The part of a plan's lds_cap that is used (a longer N(prev) is searched in place, as past any
-// lds_cap): at most what a block has room for beside its other areas, and up to the default of
-// 512 what leaves room for four blocks per CU (with three, 512 entries: 0.74 ms for 100003
-// walkers x 33 steps at scale 18 on the default plan, 0.69 ms with four).
-constexpr int trial_lds_cap(int kind, int prop, bool batch, int lds_cap)
-{
-    const int other = (int)trial_lds_bytes(kind, prop, batch, kEvNone, 0), entry = (int)sizeof(int32_t) * kWavesPerBlock;
-    const int blocks = lds_cap <= 512 ? 4 : 1;
-    const int most = (160 * 1024 / blocks - other) / entry / kWave * kWave;
-    return lds_cap < most ? lds_cap : most;
-}
-
 // Launches the instance for one logic kind; see launch_walk.  Launches with counters have no
 // kEvNone form, batches no kEvHub form (the callers choose none).
 template <int KIND, bool W, int PROP, bool BATCH, bool STATS>
 static void launch_trial_ev(const WalkArgs &args, int ev, int grid, hipStream_t s)
 {
     WalkArgs a = args;
-    a.lds_cap = trial_lds_cap(KIND, PROP, BATCH, a.lds_cap);
+    a.lds_cap = trial_lds_cap(KIND, PROP, BATCH, ev, a.lds_cap);
     const size_t lds = trial_lds_bytes(KIND, PROP, BATCH, ev, a.lds_cap);
     if (!BATCH && ev == kEvHub)
         hipLaunchKernelGGL((walk_kernel<KIND, W, PROP, BATCH, STATS, BATCH ? kEvHot : kEvHub>), dim3(grid),
@@ -1134,7 +1092,7 @@ static int trial_blocks_p(bool batch, int ev, int lds_cap)
                                              : (const void *)walk_kernel<KIND, W, PROP, false, false, kEvHot>);
     int nb = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &nb, f, kBlock, trial_lds_bytes(KIND, PROP, batch, ev, trial_lds_cap(KIND, PROP, batch, lds_cap))) !=
+            &nb, f, kBlock, trial_lds_bytes(KIND, PROP, batch, ev, trial_lds_cap(KIND, PROP, batch, ev, lds_cap))) !=
         hipSuccess)
         nb = 1;
     return std::max(1, std::min(nb, trial_waves(ev)));

@@ -95,3 +95,22 @@ def test_one_step_reservoir_walks(n):
         assert t1 < 2 * t0, (t0, t1)
     finally:
         gg.close()
+
+
+@pytest.mark.parametrize("strategy,hub", [("auto", False), ("auto", True), ("rvs", False), ("rvs", True)])
+def test_lds_cap_past_its_room(strategy, hub):
+    """A plan's lds_cap above what finds room beside the kernels' other needs costs no time (with
+    fewer resident blocks for it: 2.5 times) and changes no walk."""
+    print("lds_cap", strategy, hub, flush=True)
+    g = synth.rmat(15, 16 << 15, seed=3)
+    gg = GpuGraph(g)
+    try:
+        s = fw.FW_AUTO if strategy == "auto" else fw.FW_RVS_ONLY
+        pl = oracle.Plan(d_lo=1 << 30, hub_deg=1024 if hub else 0, hub_lanes=256 if hub else 64)
+        runs = [Walks(gg, N2V, fw_plan(pl, lds_cap=cap), s, 30000, 20) for cap in (512, 2048, 8192)]
+        t = [best_us(r, 6) for r in runs]
+        for r in runs[1:]:
+            same(runs[0], r)
+        assert max(t[1:]) < 1.3 * t[0], t
+    finally:
+        gg.close()
