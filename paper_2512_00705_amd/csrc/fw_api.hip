@@ -16,6 +16,7 @@
 #include "fw_device.h"
 #include "fw_internal.h"
 #include "fw_host.h"
+#include "fw_lds.h"
 #include "fw_pool.h"
 
 namespace fw {
@@ -859,6 +860,34 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
         *ms = total;
         return FW_OK;
     };
+    // steps of the sample walks that are sampled by eRVS under plan p
+    auto rvs_steps = [&](const fw_plan &p, uint64_t *steps) -> int {
+        DevBuf d_stats;
+        unsigned long long st[FW_NSTATS];
+        HIP_TRY(fw::dev_malloc(&d_stats.p, sizeof(st)));
+        HIP_TRY(hipMemsetAsync(d_stats.p, 0, sizeof(st), s));
+        for (int32_t i = 0; i < n_logics; ++i) {
+            const int r = fw_walk(g, &logics[i], &p, FW_AUTO, (const int32_t *)d_starts.p, n, L, 7 + (uint64_t)i,
+                                  (int32_t *)d_paths.p, (int32_t *)d_len.p, (uint64_t *)d_stats.p, stream);
+            if (r != FW_OK) return r;
+        }
+        HIP_TRY(hipMemcpyAsync(st, d_stats.p, sizeof(st), hipMemcpyDeviceToHost, s));
+        HIP_TRY(hipStreamSynchronize(s));
+        *steps = st[fw::kStRvs] + st[fw::kStFallback];
+        return FW_OK;
+    };
+    // whether AUTO launches of the logics stage other lengths of N(prev) under plan p than under b
+    auto stages_other = [&](const fw_plan &p, const fw_plan &b) {
+        for (int32_t i = 0; i < n_logics; ++i) {
+            const fw_logic &lg = logics[i];
+            const int ev = ev_of(&p, FW_AUTO, &lg), prop = lg.weighted && g->h && p.proposal != 0 ? 1 : 0;
+            if (ev != fw::kEvNone && fw::uses_membership(lg.kind) &&
+                fw::trial_lds_cap(lg.kind, prop, batched, ev, p.lds_cap) !=
+                    fw::trial_lds_cap(lg.kind, prop, batched, ev, b.lds_cap))
+                return true;
+        }
+        return false;
+    };
     // bounds every logic accepts: 0 always; the split bound (1) when a Node2Vec logic is
     // present and the graph is symmetric; the member board (2) then, or for second-order
     // PageRank when no Node2Vec logic needs a symmetric graph that is missing
@@ -885,7 +914,7 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     if (any_weighted && g->h && g->prop) props[nprop++] = 1;
     if (any_mp && g->lprop && (!any_w_other || !g->h || g->prop)) props[nprop++] = 2;
     // cost-model constant around the profiled value for each bound and proposal, then the
-    // degree gate, the LDS budget for N(prev), the eRJS trial cap and the persistent grid
+    // degree gate, the LDS budget for N(prev), the eRJS trial cap, the eRVS fields and the persistent grid
     fw_plan bestp = *out;
     float bestt = 1e30f;
     const float rho0 = out->rho;
@@ -910,12 +939,20 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
         if ((rc = time_plan(p, &t)) != FW_OK) return rc;
         if (t < bestt) bestt = t, bestp = p;
     }
-    for (int32_t cap : {256, 1024, 2048, 4096}) {  // around the default of 512
-        fw_plan p = bestp;
-        p.lds_cap = cap;
-        float t;
-        if ((rc = time_plan(p, &t)) != FW_OK) return rc;
-        if (t < bestt) bestt = t, bestp = p;
+    // the LDS budget, around the default of 512, where the launches stage N(prev) at all (not
+    // when every step is eRJS) and a candidate changes what they stage; taken only when clearly
+    // faster, by 2 %: other launches of the plan may use it otherwise
+    uint64_t by_rvs = 0;
+    if ((rc = rvs_steps(bestp, &by_rvs)) != FW_OK) return rc;
+    if (by_rvs > 0) {
+        for (int32_t cap : {256, 1024, 2048, 4096}) {
+            fw_plan p = bestp;
+            p.lds_cap = cap;
+            if (!stages_other(p, bestp)) continue;
+            float t;
+            if ((rc = time_plan(p, &t)) != FW_OK) return rc;
+            if (t < 0.98f * bestt) bestt = t, bestp = p;
+        }
     }
     // the trial cap K: a step past it falls back to eRVS (an exact sample either way), so a
     // small cap bounds the time a lane spends where the bound is loose
@@ -927,8 +964,9 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
         if (t < bestt) bestt = t, bestp = p;
     }
     // the lanes' shared eRVS threshold: fewer key draws where eRVS scans long rows; taken
-    // only when clearly faster (by 2 %), since it changes nothing where eRVS never runs
-    {
+    // only when clearly faster (by 2 %), and only where some step is eRVS
+    if ((rc = rvs_steps(bestp, &by_rvs)) != FW_OK) return rc;
+    if (by_rvs > 0) {
         fw_plan p = bestp;
         p.rvs_share = 1;
         float t;
@@ -940,30 +978,19 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     // least 1024 or 8192 entries.  Batches and servers refuse such plans, so they are taken only
     // when some step is eRVS at all and when clearly faster, by 2 %, than both the best plan so
     // far and the same kernel with no row long enough (which may differ for its registers alone)
-    if (n_logics == 1) {
-        DevBuf d_stats;
-        unsigned long long st[FW_NSTATS];
-        HIP_TRY(fw::dev_malloc(&d_stats.p, sizeof(st)));
-        HIP_TRY(hipMemsetAsync(d_stats.p, 0, sizeof(st), s));
-        rc = fw_walk(g, &logics[0], &bestp, FW_AUTO, (const int32_t *)d_starts.p, n, L, 7, (int32_t *)d_paths.p,
-                     (int32_t *)d_len.p, (uint64_t *)d_stats.p, stream);
-        if (rc != FW_OK) return rc;
-        HIP_TRY(hipMemcpyAsync(st, d_stats.p, sizeof(st), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        if (st[fw::kStRvs] + st[fw::kStFallback] > 0) {
-            const float base = bestt;
-            for (int hl : {128, 256}) {
-                fw_plan p = bestp;
-                p.hub_lanes = hl;
-                p.hub_deg = INT32_MAX;
-                float form;
-                if ((rc = time_plan(p, &form)) != FW_OK) return rc;
-                for (int hd : {1024, 8192}) {
-                    p.hub_deg = hd;
-                    float t;
-                    if ((rc = time_plan(p, &t)) != FW_OK) return rc;
-                    if (t < bestt && t < 0.98f * std::min(base, form)) bestt = t, bestp = p;
-                }
+    if (n_logics == 1 && by_rvs > 0) {
+        const float base = bestt;
+        for (int hl : {128, 256}) {
+            fw_plan p = bestp;
+            p.hub_lanes = hl;
+            p.hub_deg = INT32_MAX;
+            float form;
+            if ((rc = time_plan(p, &form)) != FW_OK) return rc;
+            for (int hd : {1024, 8192}) {
+                p.hub_deg = hd;
+                float t;
+                if ((rc = time_plan(p, &t)) != FW_OK) return rc;
+                if (t < bestt && t < 0.98f * std::min(base, form)) bestt = t, bestp = p;
             }
         }
     }
