@@ -143,7 +143,7 @@ __global__ void __launch_bounds__(kBlock, HV > 1 ? kMinWavesHub : STATS ? kMinWa
             int32_t res = -1;
             float hres = 1.0f;
             for (int G = 8; G <= 32; G <<= 1) {
-                uint64_t &pool = G == 8 ? s8 : (G == 16 ? s16 : s32);
+                uint64_t pool = G == 8 ? s8 : (G == 16 ? s16 : s32);
                 while (pool != 0)
                     if (rvs_group_pass<KIND, W, false>(a, G, pool, 0, wid, j, prev, base, deg, pbase, pdeg, want, res,
                                                        hres))

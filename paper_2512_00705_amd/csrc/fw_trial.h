@@ -146,7 +146,7 @@ __device__ __forceinline__ RvsServed rvs_serve(const WalkArgs &a, int32_t *lds, 
     int32_t res = -1;
     float hres = 1.0f;
     for (int G = 8; G <= 32; G <<= 1) {
-        uint64_t &pool = G == 8 ? s8 : (G == 16 ? s16 : s32);
+        uint64_t pool = G == 8 ? s8 : (G == 16 ? s16 : s32);
         while (pool != 0)
             if (rvs_group_pass<KIND, W, BATCH>(a, G, pool, q, wid, j, prev, base, deg, pbase, pdeg, (uint8_t)want, res,
                                                hres)) {
@@ -189,7 +189,7 @@ __device__ __forceinline__ RvsServed rvs_serve(const WalkArgs &a, int32_t *lds, 
                                : rvs_step_hub<KIND, W, 2, false>(a, Q, m, s_wid, s_j, s_prev, s_base, s_deg, s_want,
                                                                  sw, trig, hres, merge);
         else
-            res = rvs_step<KIND, W, false>(a, Q, m, s_wid, s_j, s_prev, s_base, s_deg, s_want, sw, trig, hres, merge);
+            res = rvs_step<KIND, W, true>(a, Q, m, s_wid, s_j, s_prev, s_base, s_deg, s_want, sw, trig, hres, merge);
         if (lane == src) out = {res, hres, trig};
     }
     return out;

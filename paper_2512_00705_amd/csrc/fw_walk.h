@@ -81,10 +81,12 @@ __device__ __forceinline__ StepW step_weights(const QueryDev &Q, int32_t dv, int
 
 // Transition weight w~ = w * h of the edge at CSR position k (record e) at step j
 // (Section 2.1, Eq. prob; Eq. node2vec; MetaPath rule; Eq. 2ndpr).  `m` holds N(prev)
-// sorted; `sw` the step's weights.
+// sorted; `sw` the step's weights, by value: through a reference the compiler makes of the three
+// branches one load of a chosen address, with the weights in scratch memory, and every edge of
+// a scan waits for it.
 template <int KIND, bool W>
 __device__ __forceinline__ float edge_weight(const WalkArgs &a, const QueryDev &Q, int64_t k, uint2 e, int j,
-                                             int32_t prev, const Mem &m, uint8_t want, const StepW &sw)
+                                             int32_t prev, const Mem &m, uint8_t want, StepW sw)
 {
     const float hv = W ? __uint_as_float(e.y) : 1.0f;
     if (KIND == kSecondPR) {
@@ -170,16 +172,15 @@ __device__ __forceinline__ bool merge_member(const Mem &m, int32_t u, bool valid
     return found;
 }
 
-// merge_member for the eRVS-only kernel variant, same results.  The block of N(prev) at
+// merge_member for rows scanned by 64 lanes and for the eRVS-only kernel, same results.  The block of N(prev) at
 // the cursor is loaded before the items are first used (it does not depend on them), so
 // that its load overlaps the load of the round's edges instead of following it.  Of the
 // block, only entries within [smallest item, largest item] can equal an item; when there
 // are few (a hub row scanned against a shorter N(prev): a handful per round), each is
 // broadcast from its lane and compared with every item at once, with no LDS round trip;
 // otherwise each lane bisects the block as merge_member does.  The cursor then moves past
-// every entry up to the largest item (later rounds hold only larger items).  In the other
-// kernel variants the register budget is held by the eRJS path, where the longer-lived
-// block spilled.
+// every entry up to the largest item (later rounds hold only larger items).  walk_kernel's hub
+// rows keep merge_member: there the longer-lived block spills.
 constexpr int kMergeBcast = 8;  // most in-range entries compared by broadcast (8: 2.98 s, 16: 3.01 s, 32: 3.20 s on eRVS-only scale 22)
 __device__ __forceinline__ bool merge_member_early(const Mem &m, int32_t u, bool valid, int64_t &lo)
 {
@@ -229,7 +230,7 @@ __device__ __forceinline__ bool merge_member_t(const Mem &m, int32_t u, bool val
 // Transition weight from the membership of u in N(prev) (the same expression as
 // edge_weight, for Node2Vec and second-order PageRank).
 template <int KIND, bool W>
-__device__ __forceinline__ float weight_of_member(uint2 e, int j, int32_t prev, bool member, const StepW &sw)
+__device__ __forceinline__ float weight_of_member(uint2 e, int j, int32_t prev, bool member, StepW sw)
 {
     const float hv = W ? __uint_as_float(e.y) : 1.0f;
     if (j == 0) return hv;
@@ -471,12 +472,14 @@ __device__ __forceinline__ bool rvs_group_pass(const WalkArgs &a, int G, uint64_
     const int32_t s_deg = src_of_group < 0 ? 0 : deg_of_src;
     float key = -INFINITY;
     int32_t bi = -1;
+    uint2 e = make_uint2(0u, 0u);
     if (r < s_deg) {
         const QueryDev &Q = query<BATCH>(a, s_q);
         const int64_t k = s_base + r;
         const Mem m = {a.col + s_pbase, s_pdeg, false, false};
         const StepW sw = step_weights<KIND>(Q, s_deg, s_pdeg);
-        const float wt = edge_weight<KIND, W>(a, Q, k, edge_rec(a, k), s_j, s_prev, m, s_want, sw);
+        e = edge_rec(a, k);
+        const float wt = edge_weight<KIND, W>(a, Q, k, e, s_j, s_prev, m, s_want, sw);
         const U4 x = philox(s_wid, (uint32_t)s_j, (uint32_t)r, 1u, Q.key0, Q.key1);
         key = wt > 0.0f ? ln_f(unit_uniform(x.x0)) / wt : -INFINITY;
         bi = r;
@@ -489,11 +492,12 @@ __device__ __forceinline__ bool rvs_group_pass(const WalkArgs &a, int G, uint64_
             bi = i2;
         }
     }
-    uint2 e = make_uint2(0xffffffffu, 0u);
-    if (key > -INFINITY) e = edge_rec(a, s_base + bi);
+    // the winner's edge from its lane of the group
+    const int win = g * G + (key > -INFINITY ? bi : 0);
+    const int32_t wx = __shfl((int32_t)e.x, win, kWave), wh = __shfl((int32_t)e.y, win, kWave);
     const int from = my_slot >= 0 ? my_slot * G : lane;
-    const int32_t got = __shfl((int32_t)e.x, from, kWave);
-    const uint32_t got_h = (uint32_t)__shfl((int32_t)e.y, from, kWave);
+    const int32_t got = __shfl(key > -INFINITY ? wx : -1, from, kWave);
+    const uint32_t got_h = (uint32_t)__shfl(wh, from, kWave);
     if (my_slot >= 0) {
         res = got;
         hres = W ? __uint_as_float(got_h) : 1.0f;
