@@ -356,9 +356,13 @@ hipError_t launch_walk(const WalkArgs &args, const WalkShape &w, hipStream_t s)
     // 300000 x 1: 230 and 734 us by quarters over all waves, now 112 and 268).
     const int64_t share = a.q0.L <= 1 ? waves : waves * (a.ne < 12 * a.nv ? 2 : 4);
     a.wave_lanes = (int32_t)std::min<int64_t>(kWave, (a.n + share - 1) / share);
-    // walk_kernel: a launch that the lanes hold whole is shared out over the waves; of a larger
-    // one seven eighths, the rest goes by the counter to the waves that are done first
-    const bool whole = a.n <= waves * kWave;
+    // walk_kernel: a launch of up to a quarter more walkers than lanes is shared out over the waves;
+    // of a larger one seven eighths, the rest goes by the counter to the waves that are done first.
+    // The counter's round trips take longer than a short walk: at 300000 walkers on 262144 lanes
+    // MetaPath by label groups, 40 steps at scale 14, takes 171 us whole and 271 by the counter,
+    // Node2Vec on the default plan, 20 steps at scale 18, 1.33 and 1.40 ms; at twice the lanes whole
+    // is slower (default plan, 500000: 2.08 and 1.90 ms).
+    const bool whole = a.n <= waves * kWave * 5 / 4;
     a.static_n = whole ? a.n : a.n - a.n / 8;
     a.static_waves = waves;
     a.static_each = a.static_n / waves;

@@ -114,3 +114,22 @@ def test_lds_cap_past_its_room(strategy, hub):
         assert max(t[1:]) < 1.3 * t[0], t
     finally:
         gg.close()
+
+
+@pytest.mark.parametrize("over", [1.01, 1.2])
+def test_a_few_more_walkers_than_lanes(over):
+    """A launch of a fifth more walkers than the kernel has lanes takes less than 1.5 times one that
+    they hold (with the fifth handed out by the counter: 1.6 to 1.7 times)."""
+    print("over", over, flush=True)
+    g = synth.rmat(14, 16 << 14, seed=3, nlabels=5)
+    gg = GpuGraph(g, label_alias=True)
+    try:
+        lanes = torch.cuda.get_device_properties(0).multi_processor_count * 4 * 4 * 64
+        pl = fw_plan(oracle.Plan(rho=0.4, proposal=2))
+        held = Walks(gg, MP, pl, fw.FW_AUTO, lanes - 64, 40)
+        more = Walks(gg, MP, pl, fw.FW_AUTO, int(lanes * over), 40)
+        t0, t1 = best_us(held), best_us(more)
+        print("us", t0, t1, flush=True)
+        assert t1 < 1.5 * t0, (t0, t1)
+    finally:
+        gg.close()
