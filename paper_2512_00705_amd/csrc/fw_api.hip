@@ -161,11 +161,11 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
 
     // validate on the device: row pointers first (they bound every later access)
     // [0] error bits, [1] max degree, [2] entries that do not ascend, [3] those that start a row,
-    // [4] entries with a smaller neighbour less those with a greater one
+    // [4] rows that begin with zeros, [5] entries with a smaller neighbour less those with a greater one
     unsigned long long *chk = g->scratch;
     int host_err = 0;
-    unsigned long long host_chk[5] = {};
-    static_assert(4 + fw::kQueueWords >= 5, "the scratch words hold the checks");
+    unsigned long long host_chk[6] = {};
+    static_assert(4 + fw::kQueueWords >= 6, "the scratch words hold the checks");
     hipError_t e = hipMemset(chk, 0, sizeof(host_chk));
     if (e == hipSuccess) e = fw::launch_validate_rows(g->row_ptr, g->nv, g->ne, (int *)chk, nullptr);
     if (e == hipSuccess) e = hipMemcpy(host_chk, chk, sizeof(host_chk), hipMemcpyDeviceToHost);
@@ -191,14 +191,15 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
                     "fw_graph_create: col must be in [0, nv) and strictly ascending per row; h finite and >= 0");
     }
     g->max_deg = (int64_t)host_chk[1];
+    g->zero_rows = (int64_t)host_chk[4] > g->nv / 1024;
     // symmetry decides whether the split eRJS bound may be used; not an error
-    e = fw::launch_check_symmetry(g->row_ptr, g->col, g->h, g->nv, g->ne, (int *)chk, chk + 4, nullptr);
+    e = fw::launch_check_symmetry(g->row_ptr, g->col, g->h, g->nv, g->ne, (int *)chk, chk + 5, nullptr);
     if (e == hipSuccess) e = hipMemcpy(host_chk, chk, sizeof(host_chk), hipMemcpyDeviceToHost);
     if (e != hipSuccess) {
         graph_free(g);
         return fail(FW_E_DEVICE, "fw_graph_create: %s", hipGetErrorString(e));
     }
-    g->symmetric = (host_chk[0] & 16u) == 0 && host_chk[4] == 0;
+    g->symmetric = (host_chk[0] & 16u) == 0 && host_chk[5] == 0;
     e = fw::launch_layout(g->row_ptr, g->col, g->h, g->nv, g->ne, g->edges, g->vrec, g->start_hi, nullptr);
     if (e == hipSuccess && packed) e = fw::launch_pack8(g->col, (const uint8_t *)codes.p, g->ne, g->erec8, nullptr);
     if (e == hipSuccess) e = hipMemset(g->scratch, 0, (4 + fw::kQueueWords) * sizeof(unsigned long long));
@@ -464,10 +465,17 @@ void fw::host::plan_args(const fw_plan *pl, int32_t strategy, fw::WalkArgs &a)
     a.rvs_share = pl->rvs_share;
 }
 
-int fw::host::ev_of(const fw_plan *pl, int32_t strategy, const fw_logic *lg)
+int fw::host::ev_of(const fw_graph *g, const fw_plan *pl, int32_t strategy, const fw_logic *lg)
 {
     if (pl->hub_deg > 0 && pl->hub_lanes > 64) return fw::kEvHub;
-    if (pl->rjs_cap < 64) return fw::kEvHot;  // steps that reach the trial cap go to eRVS
+    // A walk that meets an eRVS step in a launch without the scan is parked and run on by another,
+    // which pays for few.  Steps that reach the trial cap go to eRVS, whatever the cap all of them
+    // at a row without the wanted label, and so do rows whose weights are all 0 (290000 MetaPath
+    // walkers x 1 step, uniform proposals: 394 us without the scan, 88 with it; Node2Vec with
+    // records, 400000 x 5, one row in a hundred all 0: 275 and 225; in a batch without such rows
+    // 4.10 and 4.23 ms).
+    if (pl->rjs_cap < 64 || (lg->kind == FW_METAPATH && pl->proposal != 2)) return fw::kEvHot;
+    if (lg->weighted && g->h && g->zero_rows) return fw::kEvHot;
     if (strategy == FW_RJS_ONLY) return fw::kEvNone;
     if (strategy != FW_AUTO || pl->d_lo > 1) return fw::kEvHot;
     // Eq. (runtime) sends a step to eRJS iff rho * (board area) < deg * S^, S^ = mean(w) * h_SUM
@@ -522,7 +530,7 @@ int fw_walk(fw_graph *g, const fw_logic *lg, const fw_plan *pl, int32_t strategy
     a.q0.key0 = (uint32_t)seed;
     a.q0.key1 = (uint32_t)(seed >> 32);
     a.nq = 1;
-    const fw::WalkShape w = fw::walk_shape(a, lg->kind, weighted, false, ev_of(pl, strategy, lg), n, pl->grid);
+    const fw::WalkShape w = fw::walk_shape(a, lg->kind, weighted, false, ev_of(g, pl, strategy, lg), n, pl->grid);
     HIP_TRY(fw::launch_walk(a, w, (hipStream_t)stream));
     return ok();
 }
@@ -880,7 +888,7 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
     auto stages_other = [&](const fw_plan &p, const fw_plan &b) {
         for (int32_t i = 0; i < n_logics; ++i) {
             const fw_logic &lg = logics[i];
-            const int ev = ev_of(&p, FW_AUTO, &lg), prop = lg.weighted && g->h && p.proposal != 0 ? 1 : 0;
+            const int ev = ev_of(g, &p, FW_AUTO, &lg), prop = lg.weighted && g->h && p.proposal != 0 ? 1 : 0;
             if (ev != fw::kEvNone && fw::uses_membership(lg.kind) &&
                 fw::trial_lds_cap(lg.kind, prop, batched, ev, p.lds_cap) !=
                     fw::trial_lds_cap(lg.kind, prop, batched, ev, b.lds_cap))
@@ -1002,8 +1010,8 @@ int fw_plan_autotune_mix(fw_graph *g, const fw_logic *logics, int32_t n_logics, 
         fw::WalkArgs a;
         fill_args(g, &logics[0], a);
         plan_args(&bestp, FW_AUTO, a);
-        int ev = ev_of(&bestp, FW_AUTO, &logics[0]);
-        for (int32_t i = 1; i < n_logics; ++i) ev = std::max(ev, ev_of(&bestp, FW_AUTO, &logics[i]));
+        int ev = ev_of(g, &bestp, FW_AUTO, &logics[0]);
+        for (int32_t i = 1; i < n_logics; ++i) ev = std::max(ev, ev_of(g, &bestp, FW_AUTO, &logics[i]));
         const int full = fw::walk_shape(a, logics[0].kind, logics[0].weighted && g->h, batched, ev, nw, 0).grid;
         for (int gr : {full / 2, full * 2}) {
             if (gr < 1) continue;
@@ -1115,7 +1123,7 @@ int fw_batch_create(fw_graph *g, const fw_query *qs, int64_t nq, const fw_plan *
     b->a.queries = b->d_queries;
     b->a.nq = (int32_t)nq;
     int ev = fw::kEvNone;
-    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(pl, strategy, &qs[i].logic));
+    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
     b->shape = fw::walk_shape(b->a, nq > 0 ? qs[0].logic.kind : FW_NODE2VEC, weighted, true, ev, total, pl->grid);
     *out = b;
     return ok();
@@ -1260,7 +1268,7 @@ int fw_batch_run_noalloc(fw_graph *g, const fw_query *qs, int64_t nq, const fw_p
     a.queries = tab;
     a.nq = (int32_t)nq;
     int ev = fw::kEvNone;
-    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(pl, strategy, &qs[i].logic));
+    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
     HIP_TRY(fw::launch_walk(a, fw::walk_shape(a, qs[0].logic.kind, weighted, true, ev, total, pl->grid), s));
     return ok();
 }

@@ -24,6 +24,7 @@ struct fw_graph {
     uint32_t *start_hi = nullptr;           // high row-start bits, only when ne >= 2^32
     unsigned long long *scratch = nullptr;  // [1] error flag (int), [4..] walker queue (kQueueWords)
     bool prepped = false;
+    bool zero_rows = false;                 // more than one row in 1024 begins with weights of 0 only
     bool symmetric = false;                 // every (v, u) has a reverse (u, v) with equal h
     unsigned long long *mtab = nullptr;     // edge index: 64-byte buckets of 5 keys v << 32 | u and their h, or null
     uint4 *prop = nullptr;                  // h-proportional proposal records (kPropU4 uint4 per entry), or null
@@ -52,9 +53,9 @@ void fill_query(const fw_logic *lg, QueryDev &q);
 // Graph fields and logic-derived fields of a launch.
 void fill_args(const fw_graph *g, const fw_logic *lg, WalkArgs &a);
 void plan_args(const fw_plan *pl, int32_t strategy, WalkArgs &a);
-// How walk_kernel keeps eRVS for this plan, strategy and logic (Ev): kEvNone when every
-// step at a vertex with some weight goes to eRJS.
-int ev_of(const fw_plan *pl, int32_t strategy, const fw_logic *lg);
+// How walk_kernel keeps eRVS for this graph, plan, strategy and logic (Ev): kEvNone when nearly
+// every step goes to eRJS.
+int ev_of(const fw_graph *g, const fw_plan *pl, int32_t strategy, const fw_logic *lg);
 
 }  // namespace host
 }  // namespace fw

@@ -52,7 +52,7 @@ constexpr int kMinWavesRvsOnly = 7;
 // on by a kEvHot launch), kEvHot otherwise, kEvHub with hub lanes (P = 128 or 256 on long rows).
 enum Ev : int { kEvNone = 0, kEvHot = 1, kEvHub = 2 };
 
-constexpr int kQueueWords = 4;  // walker counter, parked flag, the resuming launch's counter, unused
+constexpr int kQueueWords = 2;  // walker counter, parked flag
 
 // Per-query constants of a walk job.  Float constants are prepared on the host in float32
 // exactly as the definition states, so every float32 evaluation agrees bit for bit.
@@ -209,7 +209,8 @@ hipError_t launch_check_symmetry(const int64_t *row_ptr, const int32_t *col, con
                                  int *err, unsigned long long *balance, hipStream_t s);
 hipError_t launch_validate_rows(const int64_t *row_ptr, int64_t nv, int64_t ne, int *err, hipStream_t s);
 // Sets bit 2 of *err when a neighbour is out of range or an h not finite and >= 0; the rows are
-// strictly ascending iff cnt[0] == cnt[1] (both zero on entry).  *max_deg: the longest row.
+// strictly ascending iff cnt[0] == cnt[1] (all three zero on entry); cnt[2] counts rows that begin
+// with weights of 0 only.  *max_deg: the longest row.
 hipError_t launch_validate_edges(const int64_t *row_ptr, const int32_t *col, const float *h, int64_t nv, int64_t ne,
                                  int *err, unsigned long long *max_deg, unsigned long long *cnt, hipStream_t s);
 hipError_t launch_profile(const WalkArgs &a, int kind, bool weighted, bool rjs_style, const int32_t *nodes,

@@ -163,14 +163,15 @@ __device__ __forceinline__ int64_t rows_of_entries(const int64_t *row_ptr, int64
 }
 
 // cnt[0] counts the entries that do not ascend from the entry before them, cnt[1] those of them
-// that start a row: the rows are strictly ascending iff both are equal.  Reads col and h once, in
+// that start a row: the rows are strictly ascending iff both are equal.  cnt[2] counts rows whose
+// first entries (up to 64) all weigh 0.  Reads col and h once, in
 // order (scale 20: 0.36 ms; with a wave per row 3.6).
 __global__ void __launch_bounds__(kBlock) validate_edges_kernel(const int64_t *row_ptr, const int32_t *col,
                                                                 const float *h, int64_t nv, int64_t ne, int *err,
                                                                 unsigned long long *max_deg, unsigned long long *cnt)
 {
     const int64_t stride = (int64_t)gridDim.x * kBlock, t0 = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-    unsigned long long falls = 0, row_falls = 0, dmax = 0;
+    unsigned long long falls = 0, row_falls = 0, zeros = 0, dmax = 0;
     bool bad = false;
     for (int64_t k = t0; k < ne; k += stride) {
         const int32_t c = col[k];
@@ -185,14 +186,22 @@ __global__ void __launch_bounds__(kBlock) validate_edges_kernel(const int64_t *r
         const int64_t b = row_ptr[v], e = row_ptr[v + 1];
         dmax = (unsigned long long)(e - b) > dmax ? (unsigned long long)(e - b) : dmax;
         if (b > 0 && b < e && col[b - 1] >= col[b]) ++row_falls;
+        if (h && b < e) {
+            int64_t k = b;
+            const int64_t to = e - b < kWave ? e : b + kWave;
+            while (k < to && h[k] == 0.0f) ++k;
+            if (k == to) ++zeros;
+        }
     }
     falls = wave_sum_u64(falls);
     row_falls = wave_sum_u64(row_falls);
+    zeros = wave_sum_u64(zeros);
     for (int d = kWave / 2; d > 0; d >>= 1) dmax = max(dmax, (unsigned long long)__shfl_xor((long long)dmax, d, kWave));
     if (__ballot(bad) != 0 && lane_id() == 0) atomicOr(err, 2);
     if (lane_id() == 0) {
         if (falls != 0) atomicAdd(cnt, falls);
         if (row_falls != 0) atomicAdd(cnt + 1, row_falls);
+        if (zeros != 0) atomicAdd(cnt + 2, zeros);
         if (dmax > 0) atomicMax(max_deg, dmax);
     }
 }

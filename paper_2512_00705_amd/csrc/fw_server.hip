@@ -271,7 +271,7 @@ int tick(fw_server *s, int moves)
             d.key1 = (uint32_t)(r->seed >> 32);
             p.total += r->n;
             p.lg0 = &r->logic;
-            p.ev = std::max(p.ev, fw::host::ev_of(&s->plan, s->strategy, p.lg0));
+            p.ev = std::max(p.ev, fw::host::ev_of(s->g, &s->plan, s->strategy, p.lg0));
         }
         if (p.total > 0)
             s->h_moves[moves++] = {(const int32_t *)tab, (int32_t *)(s->d_table + (size_t)grp * s->max_active),
