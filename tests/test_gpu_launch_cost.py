@@ -187,3 +187,19 @@ def test_rows_without_the_label():
         assert t[1] < 1.5 * t[0], t
     finally:
         gg.close()
+
+
+def test_short_reservoir_walks():
+    """FW_RVS_ONLY walks of a few short rows each take no longer than 1.12 times the same walks by the
+    kernel of the other strategies (with an add to the counter per finished walk: 1.3 times)."""
+    g = synth.rmat(15, 8 << 15, seed=3, nlabels=5)
+    gg = GpuGraph(g)
+    try:
+        other = Walks(gg, MP, fw_plan(oracle.Plan(d_lo=1 << 30)), fw.FW_DEGREE_SELECT, 180000, 5)
+        rvs = Walks(gg, MP, fw_plan(oracle.Plan()), fw.FW_RVS_ONLY, 180000, 5)
+        t0, t1 = best_us(other), best_us(rvs)
+        same(other, rvs)
+        print("us", t0, t1, flush=True)
+        assert t1 < 1.12 * t0, (t0, t1)
+    finally:
+        gg.close()
