@@ -329,10 +329,13 @@ WalkShape walk_shape(const WalkArgs &a, int kind, bool weighted, bool batch, int
     // Never more waves than walkers: few walkers get one lane or a few per wave, since a wave
     // serves its lanes' eRVS steps one after another.  Where every step is eRJS there is nothing
     // to serve, and beyond kSpread waves per SIMD half-empty waves only compete for issue slots.
-    // So do eRVS walks of one step: see launch_walk.
+    // So do eRVS walks of one step: see launch_walk.  Second-order PageRank with gamma = 0 weighs all
+    // neighbours alike, so its uniform proposals reject few (25000 x 40 at scale 12: 240 us on twice
+    // the waves, 200 so).
     int64_t need = std::max<int64_t>(1, (n + kWavesPerBlock - 1) / kWavesPerBlock);
     const bool one = !batch && a.strategy == kRvsOnly && a.q0.L <= 1;
-    if (one || (trials_only && (kind == kNode2Vec || a.proposal != 0)))
+    const bool first_order = kind == kSecondPR && a.q0.gamma == 0.0f;
+    if (one || (trials_only && (kind == kNode2Vec || a.proposal != 0 || first_order)))
         need = std::max(std::min(need, (int64_t)cus * (one ? 1 : kSpread)), (n + kBlock - 1) / kBlock);
     w.grid = plan_grid > 0 ? plan_grid : (int)std::min(full, need);
     w.resident = (int)std::min<int64_t>(full, w.grid);

@@ -203,3 +203,19 @@ def test_short_reservoir_walks():
         assert t1 < 1.12 * t0, (t0, t1)
     finally:
         gg.close()
+
+
+def test_first_order_pagerank():
+    """Second-order PageRank with gamma = 0 weighs all neighbours alike, as Node2Vec with p = q = 1: with
+    uniform proposals its walks take no longer than 1.12 times (spread over twice the waves: 1.24)."""
+    g = synth.rmat(12, 16 << 12, seed=3)
+    gg = GpuGraph(g, index=True)
+    try:
+        pl = fw_plan(oracle.Plan(rho=0.4))
+        n2v = oracle.Logic(kind=oracle.NODE2VEC, weighted=True, p=1.0, q=1.0)
+        pr = oracle.Logic(kind=oracle.SECOND_PR, weighted=True, gamma=0.0)
+        t0, t1 = (best_us(Walks(gg, lg, pl, fw.FW_AUTO, 25000, 40)) for lg in (n2v, pr))
+        print("us", t0, t1, flush=True)
+        assert t1 < 1.12 * t0, (t0, t1)
+    finally:
+        gg.close()
