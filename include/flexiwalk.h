@@ -187,10 +187,17 @@ typedef struct fw_plan {
 int fw_graph_create(const fw_csr *g, fw_graph **out);
 
 /* Free a graph and its device memory.  NULL is accepted.  The caller must ensure no
- * work that uses the graph is still running.  The library keeps at most 8 GiB of such
- * memory per process for the next graphs; blocks that eight graphs in a row had no use for
- * go back to the driver, and all of it when one of the library's allocations fails. */
+ * work that uses the graph is still running.  In a process that has made a graph after
+ * destroying one, the library keeps at most 8 GiB of such memory for the next graphs; blocks
+ * that eight graphs in a row had no use for go back to the driver, and all of it when one of
+ * the library's allocations fails or at fw_memory_release.  Until then (a process's first
+ * graphs) the memory goes back at once. */
 int fw_graph_destroy(fw_graph *g);
+
+/* Give the memory kept for the next graphs back to the driver, for a program that has made its
+ * last graph and needs the memory elsewhere.  Graphs that live are not touched; memory is kept
+ * again once a graph is made after one destroyed from then on.  Not during a stream capture. */
+int fw_memory_release(void);
 
 /* Per-node preprocessing (Section 4.2, preprocess()): h_MAX[v] = max h over N(v) and
  * h_SUM[v] = sum of h over N(v) accumulated in double precision and rounded once to

@@ -25,7 +25,7 @@ FW_NOALLOC_MAX_QUERIES = 4096
 FW_NSTATS = 8
 STAT_NAMES = ("steps", "rjs_steps", "rvs_steps", "rjs_fallbacks", "rjs_trials", "rvs_triggers",
               "ended_early", "alg_bytes")
-EXPORTED = ("fw_graph_create", "fw_graph_destroy", "fw_graph_preprocess", "fw_graph_build_index",
+EXPORTED = ("fw_graph_create", "fw_graph_destroy", "fw_memory_release", "fw_graph_preprocess", "fw_graph_build_index",
             "fw_graph_export_aux", "fw_graph_export_alias", "fw_graph_info", "fw_calibrate_random_reads", "fw_graph_build_alias", "fw_graph_build_label_alias",
             "fw_logic_node2vec", "fw_logic_metapath", "fw_logic_second_pr", "fw_plan_default", "fw_plan_profile",
             "fw_plan_autotune", "fw_plan_autotune_mix", "fw_walk", "fw_graph_check", "fw_last_error", "fw_batch_create", "fw_batch_launch",
@@ -75,6 +75,7 @@ def _load():
     sig = {
         "fw_graph_create": ([ctypes.POINTER(fw_csr), ctypes.POINTER(ctypes.c_void_p)], ctypes.c_int),
         "fw_graph_destroy": ([P], ctypes.c_int),
+        "fw_memory_release": ([], ctypes.c_int),
         "fw_graph_preprocess": ([P, P], ctypes.c_int),
         "fw_graph_build_index": ([P, P], ctypes.c_int),
         "fw_graph_build_alias": ([P, P], ctypes.c_int),
@@ -162,6 +163,11 @@ def fw_graph_create(nv: int, ne: int, row_ptr, col, h=None, label=None, on_devic
 
 def fw_graph_destroy(g: int):
     _check(_lib.fw_graph_destroy(g))
+
+
+def fw_memory_release():
+    """Give device memory kept for the next graphs back to the driver."""
+    _check(_lib.fw_memory_release())
 
 
 def fw_graph_preprocess(g: int, stream=None):

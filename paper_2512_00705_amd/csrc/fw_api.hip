@@ -65,7 +65,6 @@ static void graph_free(fw_graph *g)
                     (void *)g->erec8, (void *)g->vrec, (void *)g->start_hi, (void *)g->mtab, (void *)g->prop,
                     (void *)g->lrow, (void *)g->lprop})
         fw::dev_pool().free(p, unused);
-    fw::dev_pool().turn();
     delete g;
 }
 
@@ -114,6 +113,7 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
     if (in->h8 && !(in->h_scale > 0.0f && in->h_scale <= FLT_MAX))
         return fail(FW_E_INVALID, "fw_graph_create: h_scale must be finite and > 0 with h8");
 
+    fw::dev_pool().made();
     fw_graph *g = new fw_graph();
     (void)hipGetDevice(&g->device);
     g->nv = in->nv;
@@ -215,7 +215,15 @@ int fw_graph_create(const fw_csr *in, fw_graph **out)
 
 int fw_graph_destroy(fw_graph *g)
 {
+    if (!g) return ok();
     graph_free(g);
+    fw::dev_pool().turn();
+    return ok();
+}
+
+int fw_memory_release(void)
+{
+    fw::dev_pool().release();
     return ok();
 }
 

@@ -1,9 +1,14 @@
-// Device memory of graphs and of their builds, kept for the next graph.
+// Device memory of graphs and of their builds, kept for the next graph in processes that make
+// graphs one after another.
 //
 // The driver wipes freed device memory before it hands it out again and hipMalloc waits for that:
 // a program that creates, builds, walks and destroys a scale-20 graph of 31 M entries (4.2 GB a
 // turn) took 10.7 ms a turn for the first 60 turns and 114 ms on average over 400, single
 // hipMalloc calls up to 3 s; with blocks kept 8.8.
+//
+// Memory that is kept is memory that nothing else in the process, and no other process, can have.
+// So a process that has not made a graph after destroying one keeps nothing: what it frees goes
+// to the driver at once.  release() gives all back at any time and starts anew.
 //
 // Blocks of at least 1 MiB go to a list of idle blocks when they are freed, and a request takes
 // the smallest idle block of its device that is at most 1/7 larger.  Bounds: 8 GiB and
@@ -79,7 +84,7 @@ public:
                     live_[i] = live_[--live_n_];
                     break;
                 }
-            if (!unused || b.bytes == 0 || b.bytes > kMost) {
+            if (!unused || !keep_ || b.bytes == 0 || b.bytes > kMost) {
                 out[n++] = b;
             } else {
                 while (idle_n_ == kIdleBlocks || held_ + b.bytes > kMost) out[n++] = take(0);  // the oldest
@@ -90,6 +95,13 @@ public:
         for (int i = 0; i < n; ++i) (void)hipFree(out[i].p);
     }
 
+    // a graph is made
+    void made()
+    {
+        std::lock_guard<std::mutex> lk(mu_);
+        keep_ = keep_ || destroyed_;
+    }
+
     // a graph was destroyed: blocks that nobody took for long go back
     void turn()
     {
@@ -97,8 +109,22 @@ public:
         int n = 0;
         {
             std::lock_guard<std::mutex> lk(mu_);
+            destroyed_ = true;
             ++turn_;
             while (idle_n_ > 0 && turn_ - idle_[0].turn > kIdleTurns) out[n++] = take(0);
+        }
+        for (int i = 0; i < n; ++i) (void)hipFree(out[i].p);
+    }
+
+    // all idle blocks go back, and no more are kept until a graph is made after one destroyed from now on
+    void release()
+    {
+        Block out[kIdleBlocks];
+        int n = 0;
+        {
+            std::lock_guard<std::mutex> lk(mu_);
+            keep_ = destroyed_ = false;
+            while (idle_n_ > 0) out[n++] = take(idle_n_ - 1);
         }
         for (int i = 0; i < n; ++i) (void)hipFree(out[i].p);
     }
@@ -141,6 +167,7 @@ private:
     int idle_n_ = 0, live_n_ = 0;
     size_t held_ = 0;
     uint64_t turn_ = 0;
+    bool destroyed_ = false, keep_ = false;
 };
 
 // One per process; never destroyed, since graphs may outlive the library's statics.
