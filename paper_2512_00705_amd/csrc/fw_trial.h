@@ -329,6 +329,8 @@ __device__ __forceinline__ ManyDone many_trials(ArgBlock &a, const ManyStep &m, 
     return d;
 }
 
+constexpr int kAgainMost = 3, kAgainShare = 2;  // see walk_kernel's redraws
+
 template <int KIND, bool W, int PROP, bool BATCH, bool STATS, int EV>
 __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs a)
 {
@@ -336,6 +338,9 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
     constexpr bool kLab = KIND == kMetaPath && PROP == 2;   // label-conditioned proposals
     constexpr bool kHprop = (W && PROP != 0) || kLab;       // proposals from records
     constexpr bool kStash = trial_stash(KIND, PROP);
+    // (unweighted walks whose test needs memberships reject few: 300000 x 40 at scale 12, p = q = 1,
+    // 242 us without, 253 with it)
+    constexpr bool kAgain = PROP == 0 && (W || !kMem);
     if (EV == kEvHot && a.resume && *a.parked == 0) return;  // nothing was parked
     extern __shared__ __attribute__((aligned(16))) int32_t lds_all[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -571,11 +576,10 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
                 st[kStEarly] += 1;
             }
         }
-        // an open membership test, and a member trial, looks (prev or cur, cu) up: one bucket of the
+        // An open membership test, and a member trial (mt), looks (prev or cur, cu) up: one bucket of the
         // edge index, or a search of the row.  In the same pass: a pass of its own would run all
         // of the pass's other parts for the lanes that have nothing to do there.
-        if (kMem && __ballot(res == kLook) != 0) {
-            const bool mt = was == (kHprop ? (int)kColR : (int)kCol);
+        auto look_up = [&](const bool mt) {
             const uint64_t key = edge_key(mt ? cur : prev, cu);
             bool look = res == kLook, found = false;
             float hx = 1.0f;
@@ -610,7 +614,8 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
                 st[kStTrials] += 1;
                 st[kStRjs] += res >= kAcc ? 1 : 0;
             }
-        }
+        };
+        if (kMem && __ballot(res == kLook) != 0) look_up(was == (kHprop ? (int)kColR : (int)kCol));
         apart();
         // Serving a step by the wave costs about a pass, in which each of the other lanes could
         // have had a trial: it starts once the step has taken as many as there are lanes at work
@@ -619,6 +624,54 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
         // 7.6), without lookups at half (MetaPath at scale 18: 0.77 ms, all 0.83).
         const int active = __popcll(__ballot(was != kNone));
         const int many_from = max(4, kMem ? active : active / 2);
+        // Rejected uniform proposals are drawn again within the pass while half of the lanes at work
+        // have one: a trial takes about 150 instructions here, 400 in a pass, whose other parts have
+        // nothing to do for these lanes.  The others wait, so at most kAgainMost times (Node2Vec,
+        // p = 1/4, q = 4, 109000 x 52 at scale 18: 1200 us without, 1044, 1025, 1012 us with one, two,
+        // three; while a quarter of the lanes have one: 1020 us with two, 1045 with four).  MetaPath,
+        // 100000 x 40 at scale 16: 841 -> 732 us; 61 walkers x 40: 138 -> 116.
+        if (kAgain) {
+            const int again_below = min(many_from, a.rjs_cap) - 1;
+            for (int again = 0; again < kAgainMost; ++again) {
+                bool more = res == kRej && trials < again_below;
+                const int rejected = __popcll(__ballot(more));
+                if (rejected == 0 || kAgainShare * rejected < active) break;
+                const U4 x = philox((uint32_t)wid, (uint32_t)j, (uint32_t)trials + 1u, 0u, key0(), key1());
+                const float z = unit_uniform(x.x3) * area;
+                const bool ol = KIND == kNode2Vec && bE > 0.0f && z < bE;
+                more = more && (!kMem || ol || !(z < bZ));  // (member trials by the pass)
+                if (more) {
+                    ++trials;
+                    ux = x.x2;
+                    res = kAccP;
+                    cu = prev;
+                    ch = hlast;
+                    if (!ol) {
+                        const uint64_t t = (uint64_t)x.x1 * (uint32_t)deg + (((uint64_t)x.x0 * (uint32_t)deg) >> 32);
+                        const int64_t k = base + (int64_t)(t >> 32);
+                        const uint32_t lb = KIND == kMetaPath ? now((uint32_t)a.label[k]) : 0u;
+                        const uint2 e = edge_rec(a, k);
+                        cu = (int32_t)now(e.x);
+                        ch = W ? __uint_as_float(now(e.y)) : 1.0f;
+                        if (STATS)
+                            st_bytes += (uint64_t)a.item_bytes + ((kMem && j > 0 && !mb) ? 4 * (uint64_t)probes(pdeg) : 0);
+                        const float y = unit_uniform(ux) * B;
+                        if (kMem) {
+                            const bool is_prev = cu == prev;
+                            res = y < (is_prev ? wp : wlo) * ch ? kAcc : !is_prev && y < whi * ch ? kLook : kRej;
+                        } else {
+                            res = y < (lb == want ? ch : 0.0f) ? kAcc : kRej;
+                        }
+                    }
+                    if (res != kLook) {
+                        st[kStTrials] += 1;
+                        st[kStRjs] += res >= kAcc ? 1 : 0;
+                    }
+                }
+                if (kMem && __ballot(res == kLook) != 0) look_up(false);
+            }
+            apart();
+        }
         if (res == kRej) {
             ++trials;
             op = !kLab && trials >= many_from ? kMany : kTrial;
