@@ -1131,7 +1131,10 @@ int fw_batch_create(fw_graph *g, const fw_query *qs, int64_t nq, const fw_plan *
     b->a.queries = b->d_queries;
     b->a.nq = (int32_t)nq;
     int ev = fw::kEvNone;
-    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
+    for (int64_t i = 0; i < nq; ++i) {
+        ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
+        b->a.q0.gamma = std::max(b->a.q0.gamma, qs[i].logic.gamma);
+    }
     b->shape = fw::walk_shape(b->a, nq > 0 ? qs[0].logic.kind : FW_NODE2VEC, weighted, true, ev, total, pl->grid);
     *out = b;
     return ok();
@@ -1276,7 +1279,10 @@ int fw_batch_run_noalloc(fw_graph *g, const fw_query *qs, int64_t nq, const fw_p
     a.queries = tab;
     a.nq = (int32_t)nq;
     int ev = fw::kEvNone;
-    for (int64_t i = 0; i < nq; ++i) ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
+    for (int64_t i = 0; i < nq; ++i) {
+        ev = std::max(ev, ev_of(g, pl, strategy, &qs[i].logic));
+        a.q0.gamma = std::max(a.q0.gamma, qs[i].logic.gamma);
+    }
     HIP_TRY(fw::launch_walk(a, fw::walk_shape(a, qs[0].logic.kind, weighted, true, ev, total, pl->grid), s));
     return ok();
 }

@@ -248,6 +248,7 @@ int tick(fw_server *s, int moves)
         int32_t nq = 0;
         int64_t total = 0;
         int ev = fw::kEvNone;
+        float gamma = 0.0f;  // the largest
         const fw_logic *lg0 = nullptr;
     } groups[kGroups];
     for (int grp = 0; grp < kGroups; ++grp) {
@@ -272,6 +273,7 @@ int tick(fw_server *s, int moves)
             p.total += r->n;
             p.lg0 = &r->logic;
             p.ev = std::max(p.ev, fw::host::ev_of(s->g, &s->plan, s->strategy, p.lg0));
+            p.gamma = std::max(p.gamma, r->logic.gamma);
         }
         if (p.total > 0)
             s->h_moves[moves++] = {(const int32_t *)tab, (int32_t *)(s->d_table + (size_t)grp * s->max_active),
@@ -285,6 +287,7 @@ int tick(fw_server *s, int moves)
         fw::WalkArgs a;
         fw::host::fill_args(s->g, p.lg0, a);
         fw::host::plan_args(&s->plan, s->strategy, a);
+        a.q0.gamma = p.gamma;
         a.n = p.total;
         a.queue = s->d_queue + grp;
         a.err = (int *)(s->g->scratch + 1);

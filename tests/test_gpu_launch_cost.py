@@ -219,3 +219,27 @@ def test_first_order_pagerank():
         assert t1 < 1.12 * t0, (t0, t1)
     finally:
         gg.close()
+
+
+@pytest.mark.parametrize("first", [0, 1])
+def test_first_order_pagerank_in_a_mixed_batch(first):
+    """A batch with one small gamma = 0 query takes no longer than 1.1 times its other queries alone,
+    wherever that query stands in the table."""
+    g = synth.rmat(16, 16 << 16, seed=3)
+    gg = GpuGraph(g, index=True)
+    try:
+        pl, n, L = fw_plan(oracle.Plan(rho=0.4)), 60000, 40
+        starts = torch.from_numpy(synth.uniform_starts(g["nv"], n + 1, 2)).to(DEV)
+        paths = torch.empty((n + 1) * (L + 1), dtype=torch.int32, device=DEV)
+        lengths = torch.empty(n + 1, dtype=torch.int32, device=DEV)
+        small = fw.fw_query(fw.fw_logic_second_pr(0.0, True), 1, L, 5, n, n * (L + 1), n)
+        big = fw.fw_query(fw.fw_logic_second_pr(0.5, True), n, L, 6, 0, 0, 0)
+        t = []
+        for qs in ([big], [small, big] if first else [big, small]):
+            b = fw.fw_batch_create(gg.handle, qs, pl, fw.FW_AUTO, starts, paths, lengths)
+            t.append(best_us(lambda: fw.fw_batch_launch(b)))
+            fw.fw_batch_destroy(b)
+        print("us", t, flush=True)
+        assert t[1] < 1.1 * t[0], t
+    finally:
+        gg.close()
