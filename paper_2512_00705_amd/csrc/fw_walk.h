@@ -531,10 +531,19 @@ __device__ __forceinline__ void add_stats(const WalkArgs &a, uint64_t mine)
     if (lane < kNumStats && mine != 0) atomicAdd(&a.stats[lane], (unsigned long long)mine);
 }
 
-// Adds a wave's counters to the device totals and clears them.
+// Adds a wave's counters to the device totals, one after the other, and clears them.
 __device__ __forceinline__ void flush_stats(const WalkArgs &a, uint32_t (&cnt)[kStBytes], uint64_t &bytes)
 {
-    add_stats(a, take_stats(cnt, bytes));
+    const int lane = lane_id();
+#pragma unroll
+    for (int c = 0; c < kStBytes; ++c) {
+        const uint64_t v = wave_sum_u64(cnt[c]);
+        if (lane == 0 && v != 0) atomicAdd(&a.stats[c], (unsigned long long)v);
+        cnt[c] = 0;
+    }
+    const uint64_t b = wave_sum_u64(bytes);
+    if (lane == 0 && b != 0) atomicAdd(&a.stats[kStBytes], (unsigned long long)b);
+    bytes = 0;
 }
 
 // The same once per block, at the kernel's end: sums is LDS for the block, kNumStats words per wave
