@@ -338,9 +338,6 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
     constexpr bool kLab = KIND == kMetaPath && PROP == 2;   // label-conditioned proposals
     constexpr bool kHprop = (W && PROP != 0) || kLab;       // proposals from records
     constexpr bool kStash = trial_stash(KIND, PROP);
-    // (unweighted walks whose test needs memberships reject few: 300000 x 40 at scale 12, p = q = 1,
-    // 242 us without, 253 with it)
-    constexpr bool kAgain = PROP == 0 && (W || !kMem);
     if (EV == kEvHot && a.resume && *a.parked == 0) return;  // nothing was parked
     extern __shared__ __attribute__((aligned(16))) int32_t lds_all[];
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x / kWave));
@@ -629,9 +626,12 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
         // nothing to do for these lanes.  The others wait, so at most kAgainMost times (Node2Vec,
         // p = 1/4, q = 4, 109000 x 52 at scale 18: 1200 us without, 1044, 1025, 1012 us with one, two,
         // three; while a quarter of the lanes have one: 1020 us with two, 1045 with four).  MetaPath,
-        // 100000 x 40 at scale 16: 841 -> 732 us; 61 walkers x 40: 138 -> 116.
-        if (kAgain) {
+        // 100000 x 40 at scale 16: 841 -> 732 us; 61 walkers x 40: 138 -> 116.  Unweighted, p = 1/4, q = 4
+        // again: 770 -> 693 us; where nothing is rejected the test costs 4 % (p = q = 1, 300000 x 40 at
+        // scale 12: 245 -> 255).
+        if (PROP == 0) {
             const int again_below = min(many_from, a.rjs_cap) - 1;
+#pragma unroll 1
             for (int again = 0; again < kAgainMost; ++again) {
                 bool more = res == kRej && trials < again_below;
                 const int rejected = __popcll(__ballot(more));

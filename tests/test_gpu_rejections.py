@@ -18,6 +18,8 @@ pytestmark = pytest.mark.gpu
 LOGICS = {
     "node2vec": oracle.Logic(kind=oracle.NODE2VEC, weighted=True, p=0.25, q=4.0),
     "node2vec_unweighted": oracle.Logic(kind=oracle.NODE2VEC, weighted=False, p=4.0, q=0.25),
+    "node2vec_unweighted_return": oracle.Logic(kind=oracle.NODE2VEC, weighted=False, p=0.25, q=4.0),
+    "secondpr_unweighted": oracle.Logic(kind=oracle.SECOND_PR, weighted=False, gamma=0.5),
     "secondpr": oracle.Logic(kind=oracle.SECOND_PR, weighted=True, gamma=0.9),
     "metapath": MP,
     "metapath_unweighted": oracle.Logic(kind=oracle.METAPATH, weighted=False, schema=MP.schema),
