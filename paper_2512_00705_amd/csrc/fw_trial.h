@@ -1101,11 +1101,11 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
 
     // (the waves' read slots are free: no lane waits for a read)
     if (STATS) {
-        // (Served ticks keep an add per wave and counter: per block, a tick of one step of 700 walkers
-        // takes 33 us instead of 50, and a request of 300 such ticks ends within the 10 ms for which the
-        // server's queue is expected to hold the next one back.  Ticks of 64 steps: 2.29 and 2.36 ms for
-        // 30 requests at scale 20.)
-        if (BATCH && a.tick_steps > 0) flush_stats(a, st, st_bytes);
+        // (Served ticks of one step keep an add per wave and counter: per block, such a tick of 700 walkers
+        // takes 33 us instead of 50, and a request of 300 of them ends within the 10 ms for which the
+        // server's queue is expected to hold the next one back.  With these adds 30 requests in ticks of
+        // 64 steps at scale 20 take 2.42 ms, per block 2.29.)
+        if (BATCH && a.tick_steps == 1) flush_stats(a, st, st_bytes);
         else flush_stats_block(a, st, st_bytes, reinterpret_cast<uint64_t *>(lds_all), kBufU4 * 2);
     }
 }
