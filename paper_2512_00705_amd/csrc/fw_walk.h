@@ -45,18 +45,6 @@ __device__ __forceinline__ const QueryDev &query(const WalkArgs &a, int32_t q)
     return BATCH ? a.queries[q] : a.q0;
 }
 
-// Query holding flattened walker w: the last one whose first walker is <= w.
-__device__ __forceinline__ int32_t query_of(const WalkArgs &a, int64_t w)
-{
-    int32_t lo = 0, hi = a.nq - 1;
-    while (lo < hi) {
-        const int32_t mid = (lo + hi + 1) >> 1;
-        if (a.queries[mid].first <= w) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
 // The workload weights of a step that depend on u only through u in N(prev): `mem` for
 // u in N(prev), `oth` otherwise, `ret` for u = prev, and their smallest and largest
 // (Node2Vec: 1, 1/q, 1/p from the query; second-order PageRank: the two branches of
