@@ -13,7 +13,7 @@
 // results pass through pinned host memory in two kernels per tick (moves_kernel), one before the
 // launches and one on the copy stream; results stay there until they are asked for.  With a copy
 // call per piece and results in fresh host memory, 30 requests of up to 16384 x 100 steps at
-// scale 20 took 3.97 ms, of which the walks 1.2; now 2.40.  Walker i of a
+// scale 20 took 3.97 ms, of which the walks 1.2; now 2.33.  Walker i of a
 // request draws from the request's seed with Philox counter
 // (i, step, draw, tag), so its result is the same alone, in any mix and for any tick
 // length.

@@ -622,13 +622,13 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
         const int active = __popcll(__ballot(was != kNone));
         const int many_from = max(4, kMem ? active : active / 2);
         // Rejected uniform proposals are drawn again within the pass while half of the lanes at work
-        // have one: a trial takes about 150 instructions here, 400 in a pass, whose other parts have
-        // nothing to do for these lanes.  The others wait, so at most kAgainMost times (Node2Vec,
-        // p = 1/4, q = 4, 109000 x 52 at scale 18: 1200 us without, 1044, 1025, 1012 us with one, two,
-        // three; while a quarter of the lanes have one: 1020 us with two, 1045 with four).  MetaPath,
-        // 100000 x 40 at scale 16: 841 -> 732 us; 61 walkers x 40: 138 -> 116.  Unweighted, p = 1/4, q = 4
-        // again: 770 -> 693 us; where nothing is rejected the test costs 4 % (p = q = 1, 300000 x 40 at
-        // scale 12: 245 -> 255).
+        // have one: a trial takes about 100 vector instructions here, 130 more where some lane looks
+        // up, and 400 in a pass, whose other parts have nothing to do for these lanes.  The others
+        // wait, so at most kAgainMost times (Node2Vec, p = 1/4, q = 4, 109000 x 52 at scale 18: 1200 us
+        // without, 1044, 1025, 1012 us with one, two, three; while a quarter of the lanes have one:
+        // 1020 us with two, 1045 with four).  MetaPath, 100000 x 40 at scale 16: 841 -> 732 us; 61
+        // walkers x 40: 138 -> 116.  Unweighted, p = 1/4, q = 4 again: 770 -> 693 us; where nothing is
+        // rejected the test costs 4 % (p = q = 1, 300000 x 40 at scale 12: 245 -> 255).
         if (PROP == 0) {
             const int again_below = min(many_from, a.rjs_cap) - 1;
 #pragma unroll 1
