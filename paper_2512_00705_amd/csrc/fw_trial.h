@@ -633,22 +633,27 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
             const int again_below = min(many_from, a.rjs_cap) - 1;
 #pragma unroll 1
             for (int again = 0; again < kAgainMost; ++again) {
-                bool more = res == kRej && trials < again_below;
+                const bool more = res == kRej && trials < again_below;
                 const int rejected = __popcll(__ballot(more));
                 if (rejected == 0 || kAgainShare * rejected < active) break;
                 const U4 x = philox((uint32_t)wid, (uint32_t)j, (uint32_t)trials + 1u, 0u, key0(), key1());
                 const float z = unit_uniform(x.x3) * area;
                 const bool ol = KIND == kNode2Vec && bE > 0.0f && z < bE;
-                more = more && (!kMem || ol || !(z < bZ));  // (member trials by the pass)
+                const bool mr = kMem && !ol && z < bZ;
                 if (more) {
                     ++trials;
                     ux = x.x2;
                     res = kAccP;
                     cu = prev;
                     ch = hlast;
-                    if (!ol) {
-                        const uint64_t t = (uint64_t)x.x1 * (uint32_t)deg + (((uint64_t)x.x0 * (uint32_t)deg) >> 32);
-                        const int64_t k = base + (int64_t)(t >> 32);
+                    const int32_t n = mr ? pdeg : deg;
+                    const uint64_t t = (uint64_t)x.x1 * (uint32_t)n + (((uint64_t)x.x0 * (uint32_t)n) >> 32);
+                    const int64_t k = (mr ? pbase : base) + (int64_t)(t >> 32);
+                    if (mr) {
+                        cu = now(a.col[k]);
+                        res = cu != prev ? kLook : kRej;
+                        if (STATS) st_bytes += 4 + 4 * (uint64_t)probes(deg) + (W ? 4 : 0);
+                    } else if (!ol) {
                         const uint32_t lb = KIND == kMetaPath ? now((uint32_t)a.label[k]) : 0u;
                         const uint2 e = edge_rec(a, k);
                         cu = (int32_t)now(e.x);
@@ -668,7 +673,7 @@ __global__ void __launch_bounds__(kBlock, trial_waves(EV)) walk_kernel(WalkArgs 
                         st[kStRjs] += res >= kAcc ? 1 : 0;
                     }
                 }
-                if (kMem && __ballot(res == kLook) != 0) look_up(false);
+                if (kMem && __ballot(res == kLook) != 0) look_up(mr);
             }
             apart();
         }
